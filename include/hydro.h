@@ -195,16 +195,18 @@ hy_status hy_kernel_times(hy_patch *p, double ms[2], int64_t launches[2]);
 /* Name of the stage kernel configuration in use (for profiles). */
 hy_status hy_kernel_config(hy_patch *p, char *buf, size_t len);
 
-/* Launch shape of the stage kernels: a workgroup of bx x by threads owns a
- * bx x by tile of the x-y plane and marches along z over zchunk planes (3D;
- * zchunk = 1 otherwise).  The launch shape changes no result: every shape
- * computes the same cells with the same arithmetic.  Supported tiles:
- * 64x8, 64x4, 32x8 and (FP32) 32x16 in 2D and 3D, 64x1 in 1D; a patch starts
- * with a shape picked from its size (64x8, at least ~512 workgroups, at most
- * 64 planes per chunk).  The HLLC -> HLL switch keeps a shape of its own
- * (3D FP32: 32x8, at least ~1536 workgroups; else the same): hy_get_launch_cfg
- * reports the HLL/HLLC shape, hy_set_launch_cfg sets the shape of every
- * solver, hy_autotune the shape of the solver it tunes. */
+/* Launch shape of the stage kernels.  3D: a workgroup of bx x by threads owns
+ * a bx x by tile of the x-y plane and marches along z over zchunk planes.
+ * 2D: a workgroup of bx x by threads holds bx * by / 64 wavefronts, each
+ * marching along y over rows of its own strip of 60 columns (zchunk = 1).
+ * The launch shape changes no result: every shape computes the same cells
+ * with the same arithmetic.  Supported tiles: 64x8, 64x4, 32x8 and (FP32)
+ * 32x16 in 2D and 3D, 64x1 in 1D; a patch starts with a shape picked from its
+ * size (3D: 64x8, at least ~512 workgroups, at most 64 planes per chunk; 2D:
+ * 64x4).  The HLLC -> HLL switch keeps a shape of its own (3D FP32: 32x8, at
+ * least ~1536 workgroups; else the same): hy_get_launch_cfg reports the
+ * HLL/HLLC shape, hy_set_launch_cfg sets the shape of every solver,
+ * hy_autotune the shape of the solver it tunes. */
 typedef struct {
     int bx, by, zchunk;
 } hy_launch_cfg;

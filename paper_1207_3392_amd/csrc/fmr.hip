@@ -89,7 +89,7 @@ __device__ __forceinline__ void reflux_faces(T *u, const Grid &g, const Box &b, 
             const double phi_c = cf[(int64_t)v * faces + t];
             const double corr = side == 0 ? phi_c - phi_f : phi_f - phi_c;
             T &x = u[v * g.vs + c];
-            x = (T)((double)x + corr * idq);
+            x = (T)fma_(corr, idq, (double)x);
         }
     }
 }
@@ -177,7 +177,7 @@ __global__ void __launch_bounds__(TB) k_box_rate(const T *u, Grid g, Box b, T ga
         __syncthreads();
     }
     if (threadIdx.x == 0)
-        atomicMax(&rate_bits[blockIdx.x % FMR_RATE_SLOTS], (unsigned long long)__double_as_longlong(red[0]));
+        atomicMax(&rate_bits[(blockIdx.x % FMR_RATE_SLOTS) * RATE_STRIDE], (unsigned long long)__double_as_longlong(red[0]));
 }
 
 template <int ND, typename T>

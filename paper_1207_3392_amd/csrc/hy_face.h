@@ -12,32 +12,53 @@
 namespace hy {
 namespace {
 
+// Every function here rounds the same way wherever it is inlined: contraction
+// is off and each fused multiply-add is written out.  A face that two
+// wavefronts (or the stage and the flux-replacement kernels) evaluate then has
+// one flux, bit for bit, so what one cell loses its neighbour gains.  (Left to
+// the compiler, contraction follows its basic blocks: the copies of one face
+// differed in the last place.)
+#pragma clang fp contract(off)
+
 // ---------------------------------------------------------------- math ----
 
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// 1 / x.  FP64: two Newton steps on the hardware's estimate (relative error
+// 2^-23 at most, so 2^-92 before the last rounding), 5 instructions where the
+// IEEE division sequence takes 11; x normal and not 0.
 template <typename T> __device__ __forceinline__ T rcp_(T x);
 template <> __device__ __forceinline__ float rcp_<float>(float x) { return __builtin_amdgcn_rcpf(x); }
-template <> __device__ __forceinline__ double rcp_<double>(double x) { return 1.0 / x; }
+template <> __device__ __forceinline__ double rcp_<double>(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma_(fma_(-x, r, 1.0), r, r);
+    return fma_(fma_(-x, r, 1.0), r, r);
+}
 
-// sqrt(p / rho), the sound speed divided by sqrt(gamma), evaluated as
-// p rsqrt(p rho); the solvers fold sqrt(gamma) into the signal speeds
-template <typename T> __device__ __forceinline__ T sound1_(T p, T rho);
-template <> __device__ __forceinline__ float sound1_<float>(float p, float r)
+// sqrt(p / r), evaluated as p rsqrt(p r).  FP64: the hardware's reciprocal
+// root and one Newton step give y = 1 / sqrt(p r) to about 2^-45 and s = p y;
+// the residual p - s^2 r, with s r carried in two parts, then corrects s to
+// the last rounding: 12 instructions where a division and a root take 25.
+__device__ __forceinline__ float root_ratio(float p, float r) { return p * __builtin_amdgcn_rsqf(p * r); }
+__device__ __forceinline__ double root_ratio(double p, double r)
 {
-    return p * __builtin_amdgcn_rsqf(p * r);
+    const double q = p * r;
+    double y = __builtin_amdgcn_rsq(q);
+    const double h = 0.5 * y;
+    y = fma_(fma_(-q * y, y, 1.0), h, y);
+    const double s = p * y, t = s * r;
+    const double e = fma_(-fma_(s, r, -t), s, fma_(-t, s, p));
+    return fma_(e, 0.5 * y, s);
 }
-template <> __device__ __forceinline__ double sound1_<double>(double p, double r) { return sqrt(p / r); }
 
-// c_s = sqrt(gamma p / rho), evaluated as (gamma p) rsqrt(gamma p rho)
-template <typename T> __device__ __forceinline__ T sound_(T gamma, T p, T rho);
-template <> __device__ __forceinline__ float sound_<float>(float g, float p, float r)
-{
-    float gp = g * p;
-    return gp * __builtin_amdgcn_rsqf(gp * r);
-}
-template <> __device__ __forceinline__ double sound_<double>(double g, double p, double r)
-{
-    return sqrt(g * p / r);
-}
+// sqrt(p / rho), the sound speed divided by sqrt(gamma); the solvers fold
+// sqrt(gamma) into the signal speeds
+template <typename T> __device__ __forceinline__ T sound1_(T p, T rho) { return root_ratio(p, rho); }
+
+// c_s = sqrt(gamma p / rho)
+template <typename T> __device__ __forceinline__ T sound_(T gamma, T p, T rho) { return root_ratio(gamma * p, rho); }
 
 template <typename T> __device__ __forceinline__ T max3_(T a, T b, T c) { return fmax(a, fmax(b, c)); }
 
@@ -57,26 +78,28 @@ template <int ND, typename T>
 __device__ __forceinline__ bool to_prim(const T (&u)[ND + 2], T (&w)[ND + 2], T gm1)
 {
     const T ir = rcp_(u[0]);
-    T ke = T(0);
+    w[1] = u[1] * ir;
+    T ke = u[1] * w[1];
 #pragma unroll
-    for (int d = 0; d < ND; ++d) {
+    for (int d = 1; d < ND; ++d) {
         w[1 + d] = u[1 + d] * ir;
-        ke += u[1 + d] * w[1 + d];
+        ke = fma_(u[1 + d], w[1 + d], ke);
     }
     w[0] = u[0];
-    w[ND + 1] = gm1 * (u[ND + 1] - T(0.5) * ke);
+    w[ND + 1] = gm1 * fma_(T(-0.5), ke, u[ND + 1]);
     return pos_finite(w[0]) & pos_finite(w[ND + 1]);
 }
 
-template <typename T> __device__ __forceinline__ T med3_(T a, T b, T c);
-template <> __device__ __forceinline__ float med3_<float>(float a, float b, float c)
+// The two-argument minmod: the argument nearer to zero when they share a
+// sign, else 0 (the median of x, y and 0).
+__device__ __forceinline__ float minmod_(float x, float y) { return __builtin_amdgcn_fmed3f(x, y, 0.f); }
+__device__ __forceinline__ double minmod_(double x, double y)
 {
-    return __builtin_amdgcn_fmed3f(a, b, c);
+    return fmax(fmin(x, fmax(y, 0.0)), fmin(y, 0.0));
 }
-template <> __device__ __forceinline__ double med3_<double>(double a, double b, double c)
-{
-    return fmax(fmin(a, b), fmin(fmax(a, b), c));
-}
+// The same where the arguments never differ in sign.
+__device__ __forceinline__ float minmod_same(float x, float y) { return __builtin_amdgcn_fmed3f(x, y, 0.f); }
+__device__ __forceinline__ double minmod_same(double x, double y) { return fabs(x) < fabs(y) ? x : y; }
 
 // Twice the generalised-minmod slope of eq. MinMod as a per-cell difference:
 // with a = 2 theta dm, b = dm + dp, c = 2 theta dp, MM(a, b, c) (the argument
@@ -89,7 +112,7 @@ __device__ __forceinline__ T slope2_mm(T wm, T w0, T wp, T theta2)
 {
     const T dm = w0 - wm, dp = wp - w0;
     const T a = theta2 * dm, b = dm + dp, c = theta2 * dp;
-    return med3_(med3_(a, c, T(0)), b, T(0));
+    return minmod_same(minmod_(a, c), b);
 }
 
 // The generalised-minmod slope of eq. MinMod divided by theta: scaling every
@@ -97,16 +120,18 @@ __device__ __forceinline__ T slope2_mm(T wm, T w0, T wp, T theta2)
 // MM(dm, (dm + dp) k, dp) with k = 1 / (2 theta); the face values are then
 // w +/- hs * slope with hs = theta / 2.  The factors theta leave the per-cell
 // work this way.  The middle argument b = (dm + dp) k carries the sign of
-// dm and dp whenever those two agree, so MM(dm, b, dp) = MM(MM(dm, dp), b),
-// and the two-argument minmod is med3(x, y, 0) (the argument nearer to zero
-// when they share a sign, else 0): two median instructions, the same value
+// dm and dp whenever those two agree, so MM(dm, b, dp) = MM(MM(dm, dp), b):
+// two two-argument minmods (in FP32 two median instructions), the same value
 // as med3(min3, max3, 0) bit for bit (each form selects one of its inputs).
+template <typename T>
+__device__ __forceinline__ T slope_d(T dm, T dp, T k)  // from the two differences
+{
+    return minmod_same(minmod_(dm, dp), (dm + dp) * k);
+}
 template <typename T>
 __device__ __forceinline__ T slope_mm(T wm, T w0, T wp, T k)
 {
-    const T dm = w0 - wm, dp = wp - w0;
-    const T b = (dm + dp) * k;
-    return med3_(med3_(dm, dp, T(0)), b, T(0));
+    return slope_d(w0 - wm, wp - w0, k);
 }
 
 // The per-patch constants of slope_mm and of the face values, formed the
@@ -134,17 +159,17 @@ __device__ __forceinline__ void riemann(const T (&wl)[ND + 2], const T (&wr)[ND 
     const T ul = sound1_(pl, rl), ur = sound1_(pr, rr);
     // outer speed estimates alpha_+/- = max(0, +/-lambda_+/-(L), +/-lambda_+/-(R)),
     // c = sg u
-    const T ap = max3_(T(0), sg * ul + vl, sg * ur + vr);
-    const T am = max3_(T(0), sg * ul - vl, sg * ur - vr);
+    const T ap = max3_(T(0), fma_(sg, ul, vl), fma_(sg, ur, vr));
+    const T am = max3_(T(0), fma_(sg, ul, -vl), fma_(sg, ur, -vr));
     if constexpr (SOLVER == 0) {
-        T kl = T(0), kr = T(0);
+        T kl = wl[1] * wl[1], kr = wr[1] * wr[1];
 #pragma unroll
-        for (int d = 0; d < ND; ++d) {
-            kl += wl[1 + d] * wl[1 + d];
-            kr += wr[1 + d] * wr[1 + d];
+        for (int d = 1; d < ND; ++d) {
+            kl = fma_(wl[1 + d], wl[1 + d], kl);
+            kr = fma_(wr[1 + d], wr[1 + d], kr);
         }
-        const T El = pl * inv_gm1 + T(0.5) * rl * kl;
-        const T Er = pr * inv_gm1 + T(0.5) * rr * kr;
+        const T El = fma_(pl, inv_gm1, T(0.5) * rl * kl);
+        const T Er = fma_(pr, inv_gm1, T(0.5) * rr * kr);
         // F = (a+ F_L + a- F_R - a+ a- (U_R - U_L)) / (a+ + a-).  With the
         // physical flux F = v U + P (P: p in the normal momentum, p v in the
         // energy) each side's state enters once:
@@ -160,19 +185,19 @@ __device__ __forceinline__ void riemann(const T (&wl)[ND + 2], const T (&wr)[ND 
         const T wL = pos ? ap * inv : T(0.5), wR = pos ? am * inv : T(0.5);
         const T cL = wL * (vl + am), cR = wR * (vr - ap);
         const T gL = cL * rl, gR = cR * rr;  // the coefficients of the velocities in the momentum
-        f[0] = gL + gR;
+        f[0] = fma_(cL, rl, gR);
 #pragma unroll
         for (int d = 0; d < ND; ++d) {
-            if (d == Q) f[1 + d] = gL * wl[1 + d] + (gR * wr[1 + d] + (wL * pl + wR * pr));
-            else f[1 + d] = gL * wl[1 + d] + gR * wr[1 + d];
+            if (d == Q) f[1 + d] = fma_(gL, wl[1 + d], fma_(gR, wr[1 + d], fma_(wL, pl, wR * pr)));
+            else f[1 + d] = fma_(gL, wl[1 + d], gR * wr[1 + d]);
         }
-        f[IP] = cL * El + (cR * Er + (wL * (pl * vl) + wR * (pr * vr)));
+        f[IP] = fma_(cL, El, fma_(cR, Er, fma_(wL, pl * vl, wR * (pr * vr))));
     } else {
         // Batten's middle-wave speed (eq. MiddleWaveSpeed):
         // (A v_R + B v_L + p_L - p_R) / (A + B), A = rho_R (a+ - v_R), B = rho_L (a- + v_L)
         const T ql = am + vl, qr = ap - vr;
         const T A = rr * qr, B = rl * ql;
-        const T am_ = (A * vr + (B * vl + (pl - pr))) * rcp_(A + B);
+        const T am_ = fma_(A, vr, fma_(B, vl, pl - pr)) * rcp_(A + B);
         // eq. FluxHLLC: alpha_- = 0 selects L, then alpha_+ = 0 selects R,
         // then the sign of alpha_m selects the middle state on its side
         const bool sup = (am == T(0)) | (ap == T(0));
@@ -185,17 +210,17 @@ __device__ __forceinline__ void riemann(const T (&wl)[ND + 2], const T (&wr)[ND 
         // supersonic (s_K = 0): a middle speed equal to v_K makes the middle
         // state U_K itself, so the flux below is F_K
         const T sm = sup ? vK : am_;
-        T kk = T(0);
+        T kk = wk[1] * wk[1];
 #pragma unroll
-        for (int d = 0; d < ND; ++d) kk += wk[1 + d] * wk[1 + d];
-        const T EK = pK * inv_gm1 + T(0.5) * rK * kk;
+        for (int d = 1; d < ND; ++d) kk = fma_(wk[1 + d], wk[1 + d], kk);
+        const T EK = fma_(pK, inv_gm1, T(0.5) * rK * kk);
         // middle state from the jump conditions across the K-side outer wave
         // (s_K - sm is nonzero: opposite signs, or v_K != 0 when supersonic):
         // rho* = rho_K q_K / (s_K - sm), p* = p_K + rho_K q_K (sm - v_K),
         // E* = (q_K E_K - p_K v_K + p* sm) / (s_K - sm), q_K = s_K - v_K
         const T qk = sK - vK;
         const T rq = rK * qk;
-        const T ps = pK + rq * (sm - vK);
+        const T ps = fma_(rq, sm - vK, pK);
         // F_K + s_K (U*_K - U_K) equals the physical flux of the middle state
         // (the jump conditions across the s_K wave), formed directly: mass
         // flux rho* sm, and energy flux (E* + p*) sm = (q_K E_K - p_K v_K +
@@ -205,10 +230,10 @@ __device__ __forceinline__ void riemann(const T (&wl)[ND + 2], const T (&wr)[ND 
         f[0] = fd;
 #pragma unroll
         for (int d = 0; d < ND; ++d) {
-            if (d == Q) f[1 + d] = fd * sm + ps;
+            if (d == Q) f[1 + d] = fma_(fd, sm, ps);
             else f[1 + d] = fd * wk[1 + d];
         }
-        f[IP] = (qk * EK - pK * vK + ps * sK) * ism;
+        f[IP] = fma_(ps, sK, fma_(qk, EK, -(pK * vK))) * ism;
     }
 }
 
@@ -271,15 +296,15 @@ __device__ __forceinline__ void box_faces(const T *u, const Grid &g, const Box &
         const ThetaLim<T> lim = theta_lim(theta);
 #pragma unroll
         for (int v = 0; v < ND + 2; ++v) {
-            wl[v] = w4[1][v] + lim.hs * slope_mm(w4[0][v], w4[1][v], w4[2][v], lim.k);
-            wr[v] = w4[2][v] - lim.hs * slope_mm(w4[1][v], w4[2][v], w4[3][v], lim.k);
+            wl[v] = fma_(lim.hs, slope_mm(w4[0][v], w4[1][v], w4[2][v], lim.k), w4[1][v]);
+            wr[v] = fma_(-lim.hs, slope_mm(w4[1][v], w4[2][v], w4[3][v], lim.k), w4[2][v]);
         }
         face_flux<ND, Q, SOLVER>(wl, wr, fl, sqrt_gamma(gamma), inv_gm1, false);
         double *acc = side == 0 ? acc_lo : acc_hi;
 #pragma unroll
         for (int v = 0; v < ND + 2; ++v) {
             double &a = acc[(int64_t)v * faces + t];
-            a = (assign ? 0.0 : a) + w * (double)fl[v];
+            a = fma_(w, (double)fl[v], assign ? 0.0 : a);
         }
     }
 }

@@ -32,8 +32,8 @@ enum {
 };
 
 // The CFL rate is reduced into FMR_RATE_SLOTS words (workgroup b into word
-// b mod FMR_RATE_SLOTS), so the atomics of a reduction never queue on one
-// address; readers take the max over the words.
+// b mod FMR_RATE_SLOTS, RATE_STRIDE words apart), so the atomics of a
+// reduction never queue on one line; readers take the max over the words.
 constexpr int FMR_RATE_SLOTS = 32;
 
 // One launch applies the clock updates op0 (on level l0), then op1 (on l1),

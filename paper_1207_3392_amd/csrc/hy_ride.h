@@ -72,14 +72,14 @@ __device__ __forceinline__ void clock_op(FmrClock *c, int op, int l, int nlev, u
     switch (op) {
     case CLOCK_RESET:
         for (int i = 0; i < nlev; ++i) c[i].t = 0.0;
-        for (int k = 0; k < FMR_RATE_SLOTS; ++k) rate_bits[k] = 0ull;
+        for (int k = 0; k < FMR_RATE_SLOTS; ++k) rate_bits[k * RATE_STRIDE] = 0ull;
         break;
     case CLOCK_DEEPEST:
     case CLOCK_DEEPEST_KEEP: {
         unsigned long long rb = 0ull;
         for (int k = 0; k < FMR_RATE_SLOTS; ++k) {
-            rb = rb > rate_bits[k] ? rb : rate_bits[k];
-            if (op == CLOCK_DEEPEST) rate_bits[k] = 0ull;
+            rb = rb > rate_bits[k * RATE_STRIDE] ? rb : rate_bits[k * RATE_STRIDE];
+            if (op == CLOCK_DEEPEST) rate_bits[k * RATE_STRIDE] = 0ull;
         }
         c[l].dt = dt_fixed > 0.0 ? dt_fixed : cfl / __longlong_as_double((long long)rb);
         break;
@@ -128,7 +128,7 @@ __device__ __forceinline__ void prolong_cell(const RideJob<T> &j, int sc)
         // of the parent width, so it moves by +/- slope2 / 8
         const T h = s3[q] ? T(0.125) : T(-0.125);
 #pragma unroll
-        for (int v = 0; v < ND + 2; ++v) wc[v] += h * slope2_mm(wm[v], w0[v], wp[v], T(2));
+        for (int v = 0; v < ND + 2; ++v) wc[v] = fma_(h, slope2_mm(wm[v], w0[v], wp[v], T(2)), wc[v]);
     }
     const int64_t c = at(j.fg, c3[0], c3[1], c3[2]);
     T uc[ND + 2], ke = T(0);
@@ -136,9 +136,9 @@ __device__ __forceinline__ void prolong_cell(const RideJob<T> &j, int sc)
 #pragma unroll
     for (int d = 0; d < ND; ++d) {
         uc[1 + d] = wc[0] * wc[1 + d];
-        ke += wc[1 + d] * wc[1 + d];
+        ke = fma_(wc[1 + d], wc[1 + d], ke);
     }
-    uc[ND + 1] = wc[ND + 1] * j.inv_gm1 + T(0.5) * wc[0] * ke;
+    uc[ND + 1] = fma_(wc[ND + 1], j.inv_gm1, T(0.5) * wc[0] * ke);
 #pragma unroll
     for (int v = 0; v < ND + 2; ++v) {
         j.fine[v * j.fg.vs + c] = uc[v];

@@ -291,7 +291,9 @@ void pick_config(hy_patch *p)
     const hy_patch_desc &d = p->d;
     const int64_t *n = p->padded ? p->inner : d.n;  // the extents the stages cover
     p->cfg.bx = 64;
-    p->cfg.by = d.ndim == 1 ? 1 : 8;
+    // (in 2D the tile only sets how many wavefronts share a workgroup: four
+    // place more evenly on the CUs than eight)
+    p->cfg.by = d.ndim == 1 ? 1 : (d.ndim == 2 ? 4 : 8);
 
     if (const char *e = std::getenv("HY_TILE")) {  // "BXxBY", for tuning runs
         int bx = 0, by = 0;
@@ -572,7 +574,7 @@ hy_status hy_cfl_dt(hy_patch *p, double cfl, double *dt_out)
     hy_status st = read_ctl(p, &c);
     if (st != HY_OK) return st;
     unsigned long long rb = 0ull;
-    for (int k = 0; k < hy::RATE_SLOTS; ++k) rb = std::max(rb, c.rate[p->parity][k]);
+    for (int k = 0; k < hy::RATE_SLOTS; ++k) rb = std::max(rb, c.rate[p->parity][k * hy::RATE_STRIDE]);
     const double rate = __builtin_bit_cast(double, rb);
     *dt_out = cfl / rate;
     if (c.err || !(rate > 0.0) || !std::isfinite(rate))
@@ -1630,7 +1632,7 @@ hy_status fmr_layout(const hy_fmr_desc *d, FmrLayout *L)
         o = align_up(o + sizeof(double) * 5 * (size_t)(n[1] * n[2]), 256);
     }
     L->rate = o;
-    o = align_up(o + sizeof(unsigned long long) * hy::FMR_RATE_SLOTS, 256);
+    o = align_up(o + sizeof(unsigned long long) * hy::FMR_RATE_SLOTS * hy::RATE_STRIDE, 256);
     L->clock = o;
     o = align_up(o + sizeof(hy::FmrClock) * HY_FMR_MAXLEV, 256);
     L->total = o + 256;

@@ -75,7 +75,7 @@ __global__ void __launch_bounds__(RB) k_cfl_rate(const T *u, int64_t ncell, int6
     if (threadIdx.x == 0) {
         double m = 0.0;
         for (int w = 0; w < RB / 64; ++w) m = fmax(m, sr[w]);
-        if (m > 0.0) atomicMax(&ctl->rate[slot][blockIdx.x % RATE_SLOTS], (unsigned long long)__double_as_longlong(m));
+        if (m > 0.0) atomicMax(&ctl->rate[slot][(blockIdx.x % RATE_SLOTS) * RATE_STRIDE], (unsigned long long)__double_as_longlong(m));
     }
 }
 
@@ -177,7 +177,7 @@ __global__ void __launch_bounds__(RB) k_kinetic_final(const double *partials, in
 
 __global__ void k_ctl_reset_rate(DevCtl *ctl, int slot)
 {
-    if (threadIdx.x < RATE_SLOTS) ctl->rate[slot][threadIdx.x] = 0ull;
+    if (threadIdx.x < RATE_SLOTS) ctl->rate[slot][threadIdx.x * RATE_STRIDE] = 0ull;
 }
 
 __global__ void k_ctl_init(DevCtl *ctl)
@@ -185,8 +185,8 @@ __global__ void k_ctl_init(DevCtl *ctl)
     ctl->time[0] = 0.0;
     ctl->time[1] = 0.0;
     for (int k = 0; k < RATE_SLOTS; ++k) {
-        ctl->rate[0][k] = 0ull;
-        ctl->rate[1][k] = 0ull;
+        ctl->rate[0][k * RATE_STRIDE] = 0ull;
+        ctl->rate[1][k * RATE_STRIDE] = 0ull;
     }
     ctl->err = 0u;
 }

@@ -24,6 +24,7 @@
 #include "hy_internal.h"
 #include "hy_face.h"
 #include "hy_ride.h"
+#include "hy_stage.h"
 
 #include <math.h>
 #include <type_traits>
@@ -33,55 +34,8 @@ namespace {
 
 // ------------------------------------------------------------ kernel ----
 
-template <int ND, typename T>
-__device__ __forceinline__ double stage_dt(const StageArgs<T> &a)
-{
-    if (a.dt_mode == DT_HOST) return a.dt_host;
-    if (a.dt_mode == DT_PTR) return *a.dt_dev;
-    unsigned long long rb = 0ull;
-#pragma unroll
-    for (int k = 0; k < RATE_SLOTS; ++k) rb = rb > a.ctl->rate[a.parity][k] ? rb : a.ctl->rate[a.parity][k];
-    const double rate = __longlong_as_double((long long)rb);
-    const double t = a.ctl->time[a.parity];
-    double dt = fmin(a.cfl / rate, a.t_end - t);
-    return dt > 0.0 ? dt : 0.0;
-}
-
-// A value every lane holds alike, moved to a scalar register so the vector
-// register budget of the per-cell work does not carry it.
-__device__ __forceinline__ float uniform_(float x)
-{
-    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
-}
-__device__ __forceinline__ double uniform_(double x)
-{
-    const long long b = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_readfirstlane((int)(b & 0xffffffffll));
-    const int hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
-    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-
 constexpr int FLIP = 1 << 30;      // set on a mapped index whose source is a mirror image
 constexpr int IDX = FLIP - 1;
-
-// Source of index i along a dimension of n interior cells; flip toggles when
-// the source is a mirror image.  Indices far outside the ghost range (only
-// met by the unused columns of partial tiles) are clamped into the array.
-__device__ __forceinline__ int map32(int i, int n, int bclo, int bchi, bool &flip)
-{
-    if (i >= 0 && i < n) return i;
-    int m;
-    if (i < 0) {
-        if (bclo == BC_PERIODIC) m = i + n;
-        else if (bclo == BC_OUTFLOW) m = 0;
-        else { m = -1 - i; flip = !flip; }
-    } else {
-        if (bchi == BC_PERIODIC) m = i - n;
-        else if (bchi == BC_OUTFLOW) m = n - 1;
-        else { m = 2 * n - 1 - i; flip = !flip; }
-    }
-    return m < 0 ? 0 : (m >= n ? n - 1 : m);
-}
 
 // The learned-limiter slope of variable v along q at cell (gx, gy, gz) (face
 // values w +/- slope / 2): interior slopes come from the slope array; a ghost
@@ -110,31 +64,6 @@ __device__ __forceinline__ T learned_slope(const StageArgs<T> &a, int q, int v, 
     const int c = (g[2] * (int)a.n[1] + g[1]) * (int)a.n[0] + g[0];
     const float *base = a.slopes + (int64_t)(q * (ND + 2) + v) * a.vstride;
     return sgn * (T)base[c];
-}
-
-// The face-flux workgroups of a padded launch (see BoxFluxes): workgroup fid
-// after the tiles takes (box, q, side) = segment fid / blocks, NT faces of it.
-template <int ND, int SOLVER, int NT, typename T>
-__device__ __forceinline__ void stage_box_faces(const StageArgs<T> &a, int fid, int tid)
-{
-    const int seg = fid / a.bf.blocks;
-    const int t = (fid - seg * a.bf.blocks) * NT + tid;
-    const int side = seg & 1, bq = seg >> 1, k = bq / ND, q = bq - k * ND;
-    const Grid g{{a.vm[0], a.vm[1], a.vm[2]}, a.vstride};
-    const Box &b = a.bf.b[k];
-    const double w = 0.5 * *a.dt_dev;
-    const bool as = a.bf.assign[k] != 0;
-    if (q == 0)
-        box_faces<ND, 0, SOLVER>(a.uin, g, b, t, side, a.gamma, a.gm1, a.inv_gm1, a.theta, w, as, a.bf.acc[k][0][0],
-                                 a.bf.acc[k][0][1]);
-    if constexpr (ND >= 2)
-        if (q == 1)
-            box_faces<ND, 1, SOLVER>(a.uin, g, b, t, side, a.gamma, a.gm1, a.inv_gm1, a.theta, w, as,
-                                     a.bf.acc[k][1][0], a.bf.acc[k][1][1]);
-    if constexpr (ND >= 3)
-        if (q == 2)
-            box_faces<ND, 2, SOLVER>(a.uin, g, b, t, side, a.gamma, a.gm1, a.inv_gm1, a.theta, w, as,
-                                     a.bf.acc[k][2][0], a.bf.acc[k][2][1]);
 }
 
 // At least 4 waves per SIMD: the LDS plane tile admits two 512-thread
@@ -191,7 +120,7 @@ __global__ void __launch_bounds__(BX *BY, (BX * BY == 256) ? 3 : 4) k_stage(cons
         // before any barrier)
         if ((int)blockIdx.x >= a.ntiles) {
             const int fid = (int)blockIdx.x - a.ntiles;
-            if (fid < a.nbfwg) stage_box_faces<ND, SOLVER, NT>(a, fid, tid);
+            if (fid < a.nbfwg) stage_box_faces<ND, SOLVER>(a, fid, tid, NT);
             else ride_run<ND>(a.ride, fid - a.nbfwg, tid, NT);
             return;
         }
@@ -261,7 +190,7 @@ __global__ void __launch_bounds__(BX *BY, (BX * BY == 256) ? 3 : 4) k_stage(cons
         sMap[i] = m | (f ? FLIP : 0);
     }
 
-    const double dtd = stage_dt<ND>(a);
+    const double dtd = stage_dt(a);
     const T dt = (T)dtd;
     // the step's weight of a flux difference per unit width, and of the source
     const T wdt = STAGE == 1 ? dt : T(0.5) * dt;
@@ -273,7 +202,7 @@ __global__ void __launch_bounds__(BX *BY, (BX * BY == 256) ? 3 : 4) k_stage(cons
     }
     if constexpr (STAGE == 1) {
         if (blockIdx.x == 0 && tid < RATE_SLOTS) {
-            a.ctl->rate[a.parity ^ 1][tid] = 0ull;
+            a.ctl->rate[a.parity ^ 1][tid * RATE_STRIDE] = 0ull;
             if (tid == 0) a.ctl->time[a.parity ^ 1] = a.ctl->time[a.parity] + dtd;
         }
     }
@@ -283,20 +212,18 @@ __global__ void __launch_bounds__(BX *BY, (BX * BY == 256) ? 3 : 4) k_stage(cons
     const int xm = sMap[tx + 2];
     const int ym = (ND >= 2) ? sMap[WX + ty + 2] : 0;
     const bool fxo = (xm & FLIP) != 0, fyo = (ym & FLIP) != 0;
-    const unsigned colo = (unsigned)((ym & IDX) * sx + (xm & IDX));
+    const unsigned colo = (unsigned)((ym & IDX) * sx + (xm & IDX));  // (a valid own cell maps to itself)
     const int gx = x0 + tx, gy = y0 + ty;
     const bool own_valid = (gx < nx) && (gy < ny);
-    const unsigned colv = (unsigned)((gy + vy) * sx + gx + vx);
 
     // halo cells of this thread: plane offset, LDS slot, mirror flags
     unsigned hoff[HPT];
-    int hlds[HPT], hflg[HPT];
+    int hlds[HPT];  // the slot, with the mirror flags of x and y in bits 28 and 29; -1: no cell
 #pragma unroll
     for (int j = 0; j < HPT; ++j) {
         const int h = tid + j * NT;
         hlds[j] = -1;
         hoff[j] = 0;
-        hflg[j] = 0;
         if (h < NH) {
             int row, col;
             if (h < HROW) {
@@ -312,8 +239,7 @@ __global__ void __launch_bounds__(BX *BY, (BX * BY == 256) ? 3 : 4) k_stage(cons
             const int hx = sMap[col + 2];
             const int hy = (ND >= 2) ? sMap[WX + row + 2] : 0;
             hoff[j] = (unsigned)((hy & IDX) * sx + (hx & IDX));
-            hlds[j] = (row + OY) * WX + col + 2;
-            hflg[j] = ((hx & FLIP) ? 1 : 0) | ((hy & FLIP) ? 2 : 0);
+            hlds[j] = ((row + OY) * WX + col + 2) | ((hx & FLIP) ? 1 << 28 : 0) | ((hy & FLIP) ? 1 << 29 : 0);
         }
     }
 
@@ -344,10 +270,7 @@ __global__ void __launch_bounds__(BX *BY, (BX * BY == 256) ? 3 : 4) k_stage(cons
             c = (e & 1) ? BX : -1;
         }
     };
-    const T seps = (T)SHOCK_EPS;
-    auto shock = [&](T pa, T pb, T va, T vb) -> bool {
-        return (fabs(pb - pa) > seps * fmin(pa, pb)) & (vb - va < T(0));
-    };
+    auto shock = [](T pa, T pb, T va, T vb) -> bool { return x_shock(pa, pb, va, vb); };
     // x and y bits of the cell at tile (row r, column c) of the current plane
     auto bits_w = [&](int r, int c) -> unsigned {
         unsigned b = shock(sW[IP][r + OY][c + 1], sW[IP][r + OY][c + 3], sW[1][r + OY][c + 1], sW[1][r + OY][c + 3]);
@@ -389,7 +312,7 @@ __global__ void __launch_bounds__(BX *BY, (BX * BY == 256) ? 3 : 4) k_stage(cons
     };
     auto face_state = [&](const T (&w)[NP], const T (&s)[NP], T h, T (&out)[NP]) {
 #pragma unroll
-        for (int v = 0; v < NP; ++v) out[v] = w[v] + h * s[v];
+        for (int v = 0; v < NP; ++v) out[v] = fma_(h, s[v], w[v]);
     };
     // the ring cell of this thread at plane z: pressure and the three
     // velocities, mirror signs applied (3D switch)
@@ -501,11 +424,7 @@ __global__ void __launch_bounds__(BX *BY, (BX * BY == 256) ? 3 : 4) k_stage(cons
         const unsigned zko = (ND == 3) ? (unsigned)((kz + vz) * plane) : 0u;
         bool fz2 = false;
         if constexpr (ND == 3) load(zoff(kz + 2, fz2) + colo, U2);
-        T u0[NP];  // U^n of the own cell (second stage), issued early, used in phase 3
-        if constexpr (STAGE == 2 && !LATE) {
-#pragma unroll
-            for (int v = 0; v < NP; ++v) u0[v] = own_valid ? at(u0p[v], zko + colv) : T(0);
-        }
+        T u0[NP];  // U^n of the own cell (second stage): loaded after the z face, whose registers it takes, used in phase 3
 
         // learned limiter: the own cell's x and y slopes and this thread's
         // ring slope go from the slope array straight into the LDS slope
@@ -517,7 +436,7 @@ __global__ void __launch_bounds__(BX *BY, (BX * BY == 256) ? 3 : 4) k_stage(cons
         if constexpr (LIM == LIM_LEARNED) {
             if (own_valid) {
                 // an interior cell: the slopes sit at its own offset
-                const unsigned o = zko + colv;
+                const unsigned o = zko + colo;
 #pragma unroll
                 for (int v = 0; v < NP; ++v) {
                     lsx[v] = (T)at(a.slopes + (int64_t)v * a.vstride, o);
@@ -598,10 +517,10 @@ __global__ void __launch_bounds__(BX *BY, (BX * BY == 256) ? 3 : 4) k_stage(cons
             if (hlds[j] >= 0) {
                 T w[NP];
                 to_prim<ND>(hcur[j], w, gm1);
-                if (hflg[j] & 1) w[1] = -w[1];
-                if constexpr (ND >= 2) { if (hflg[j] & 2) w[2] = -w[2]; }
+                if (hlds[j] & (1 << 28)) w[1] = -w[1];
+                if constexpr (ND >= 2) { if (hlds[j] & (1 << 29)) w[2] = -w[2]; }
 #pragma unroll
-                for (int v = 0; v < NP; ++v) sWf[v * RY * WX + hlds[j]] = w[v];
+                for (int v = 0; v < NP; ++v) sWf[v * RY * WX + (hlds[j] & ((1 << 28) - 1))] = w[v];
             }
         }
         __syncthreads();
@@ -651,7 +570,7 @@ __global__ void __launch_bounds__(BX *BY, (BX * BY == 256) ? 3 : 4) k_stage(cons
                 for (int v = 0; v < NP; ++v) Sk1[v] = slope_mm(Wk[v], Wk1[v], W2[v], lk);
             } else if (own_valid && kz + 1 < nz) {
                 // the z slope of plane kz+1: one plane up at the own offset
-                const unsigned o = zko + colv + (unsigned)plane;
+                const unsigned o = zko + colo + (unsigned)plane;
 #pragma unroll
                 for (int v = 0; v < NP; ++v) Sk1[v] = (T)at(a.slopes + (int64_t)(2 * NP + v) * a.vstride, o);
             } else {  // past the last plane, or a ghost column: boundary-mapped
@@ -730,6 +649,10 @@ __global__ void __launch_bounds__(BX *BY, (BX * BY == 256) ? 3 : 4) k_stage(cons
             return false;
         };
         if constexpr (ND == 3) redo(face_z(Main{}), [&] { (void)face_z(Hll{}); });
+        if constexpr (STAGE == 2 && !LATE) {
+#pragma unroll
+            for (int v = 0; v < NP; ++v) u0[v] = at(u0p[v], zko + colo);
+        }
         if (ring1) __builtin_amdgcn_s_setprio(0);
         __syncthreads();
         if (ring2) __builtin_amdgcn_s_setprio(3);
@@ -747,8 +670,8 @@ __global__ void __launch_bounds__(BX *BY, (BX * BY == 256) ? 3 : 4) k_stage(cons
             T wl[NP], wr[NP], fl[NP];
 #pragma unroll
             for (int v = 0; v < NP; ++v) {
-                wl[v] = sW[v][row + OY][col + 1] + hs * sSx[v][row][col];
-                wr[v] = sW[v][row + OY][col + 2] - hs * sSx[v][row][col + 1];
+                wl[v] = fma_(hs, sSx[v][row][col], sW[v][row + OY][col + 1]);
+                wr[v] = fma_(-hs, sSx[v][row][col + 1], sW[v][row + OY][col + 2]);
             }
             riemann<ND, 0, decltype(kind)::value>(wl, wr, fl, sg, igm1);
 #pragma unroll
@@ -761,8 +684,8 @@ __global__ void __launch_bounds__(BX *BY, (BX * BY == 256) ? 3 : 4) k_stage(cons
             T wl[NP], wr[NP], fl[NP];
 #pragma unroll
             for (int v = 0; v < NP; ++v) {
-                wl[v] = sW[v][row + 1][col + 2] + hs * sSy[v][row][col];
-                wr[v] = sW[v][row + 2][col + 2] - hs * sSy[v][row + 1][col];
+                wl[v] = fma_(hs, sSy[v][row][col], sW[v][row + 1][col + 2]);
+                wr[v] = fma_(-hs, sSy[v][row + 1][col], sW[v][row + 2][col + 2]);
             }
             riemann<ND, 1, decltype(kind)::value>(wl, wr, fl, sg, igm1);
 #pragma unroll
@@ -794,33 +717,33 @@ __global__ void __launch_bounds__(BX *BY, (BX * BY == 256) ? 3 : 4) k_stage(cons
         } else {
             if constexpr (LATE) {
 #pragma unroll
-                for (int v = 0; v < NP; ++v) u0[v] = own_valid ? at(u0p[v], zko + colv) : T(0);
+                for (int v = 0; v < NP; ++v) u0[v] = own_valid ? at(u0p[v], zko + colo) : T(0);
             }
 #pragma unroll
             for (int v = 0; v < NP; ++v) out[v] = T(0.5) * (u0[v] + Uk[v]);
         }
 #pragma unroll
-        for (int v = 0; v < NP; ++v) out[v] += cdt[0] * (sFx[v][ty][tx] - sFx[v][ty][tx + 1]);
+        for (int v = 0; v < NP; ++v) out[v] = fma_(cdt[0], sFx[v][ty][tx] - sFx[v][ty][tx + 1], out[v]);
         if constexpr (ND >= 2) {
 #pragma unroll
-            for (int v = 0; v < NP; ++v) out[v] += cdt[1] * (sFy[v][ty][tx] - sFy[v][ty + 1][tx]);
+            for (int v = 0; v < NP; ++v) out[v] = fma_(cdt[1], sFy[v][ty][tx] - sFy[v][ty + 1][tx], out[v]);
         }
         if constexpr (ND == 3) {
 #pragma unroll
-            for (int v = 0; v < NP; ++v) out[v] += cdt[2] * (Flo[v] - Fhi[v]);
+            for (int v = 0; v < NP; ++v) out[v] = fma_(cdt[2], Flo[v] - Fhi[v], out[v]);
         }
         if (grav) {
             // uniform acceleration: momentum += rho a, energy += S . a
-            T pw = T(0);
+            T pw = Uk[1] * cacc[0];
 #pragma unroll
             for (int d = 0; d < ND; ++d) {
-                out[1 + d] += Uk[0] * cacc[d];
-                pw += Uk[1 + d] * cacc[d];
+                out[1 + d] = fma_(Uk[0], cacc[d], out[1 + d]);
+                if (d > 0) pw = fma_(Uk[1 + d], cacc[d], pw);
             }
             out[IP] += pw;
         }
         if (own_valid) {
-            const unsigned c = zko + colv;
+            const unsigned c = zko + colo;
 #pragma unroll
             for (int v = 0; v < NP; ++v) *(T *)((char *)uout[v] + c * (unsigned)sizeof(T)) = out[v];
             if constexpr (STAGE == 2) {
@@ -866,7 +789,8 @@ __global__ void __launch_bounds__(BX *BY, (BX * BY == 256) ? 3 : 4) k_stage(cons
 #pragma unroll
             for (int w = 0; w < NT / 64; ++w) m = fmax(m, sRate[w]);
             if (m > 0.0)
-                atomicMax(&a.ctl->rate[a.parity ^ 1][blockIdx.x % RATE_SLOTS], (unsigned long long)__double_as_longlong(m));
+                atomicMax(&a.ctl->rate[a.parity ^ 1][(blockIdx.x % RATE_SLOTS) * RATE_STRIDE],
+                          (unsigned long long)__double_as_longlong(m));
         }
     }
 }
@@ -879,23 +803,9 @@ hipError_t launch_one(const LaunchCfg &cfg, StageArgs<T> a, hipStream_t s)
     const int chunks = ND == 3 ? (int)((a.n[2] + cfg.zchunk - 1) / cfg.zchunk) : 1;
     a.ntiles = a.tiles_x * a.tiles_y * chunks;
     int64_t blocks = a.ntiles;
-    a.nbfwg = 0;
     if constexpr (LIM == LIM_THETA_PADDED) {
-        if (a.bf.nbox > 0) {
-            if (a.bf.nbox > 2 || a.dt_mode != DT_PTR || !a.dt_dev) return hipErrorInvalidValue;
-            int most = 0;
-            for (int k = 0; k < a.bf.nbox; ++k)
-                for (int q = 0; q < ND; ++q) {
-                    const int r1 = q == 0 ? 1 : 0, r2 = q == 2 ? 1 : 2;
-                    most = most > a.bf.b[k].n[r1] * a.bf.b[k].n[r2] ? most : a.bf.b[k].n[r1] * a.bf.b[k].n[r2];
-                }
-            a.bf.blocks = (most + BX * BY - 1) / (BX * BY);
-            a.nbfwg = a.bf.nbox * ND * 2 * a.bf.blocks;
-            blocks += a.nbfwg;
-        }
-        const int rb = (a.ride.cells + BX * BY - 1) / (BX * BY);
-        a.ride.blocks = (a.ride.cells > 0 || a.ride.ck.c) ? (rb > 1 ? rb : 1) : 0;
-        blocks += a.ride.blocks;
+        const hipError_t e = stage_extra_blocks<ND>(a, BX * BY, &blocks);
+        if (e != hipSuccess) return e;
     }
     if (blocks > INT32_MAX) return hipErrorInvalidValue;
     hipLaunchKernelGGL((k_stage<ND, T, SOLVER, STAGE, LIM, BX, BY>), dim3((unsigned)blocks), dim3(BX, BY, 1), 0, s, a);
@@ -954,7 +864,7 @@ hipError_t launch_stage(int ndim, int solver, int stage, int limiter, const Laun
 {
     switch (ndim) {
     case 1: return launch_nd<1, T>(solver, stage, limiter, cfg, a, s);
-    case 2: return launch_nd<2, T>(solver, stage, limiter, cfg, a, s);
+    case 2: return launch_strip<T>(solver, stage, limiter, cfg, a, s);
     default: return launch_nd<3, T>(solver, stage, limiter, cfg, a, s);
     }
 }
