@@ -240,9 +240,10 @@ const char *hy_last_error(void);
  * two-stage update as hy_step.  Every description must be ndim = 1,
  * precision = 32, limiter = HY_LIM_THETA, accel = 0 and n <= 6144
  * (HY_EUNSUPPORTED / HY_EINVAL otherwise).  Tube states are concatenated in
- * the caller's workspace; a workgroup holds one tube in LDS at a time, taking
- * tubes from a device queue in descending order of n^2 max(|v| + c) / L
- * (estimated from the states given to hy_batch_set_state). */
+ * the caller's workspace; a workgroup holds one tube, or its share of a long
+ * one, in registers, taking tubes from a device queue in descending order of
+ * their time estimate (from n, max(|v| + c) / L of the states given to
+ * hy_batch_set_state).  How a tube is shared changes no result. */
 typedef struct hy_batch hy_batch;
 
 hy_status hy_batch_workspace_bytes(const hy_patch_desc *descs, int count, size_t *bytes);
@@ -253,8 +254,8 @@ hy_status hy_batch_set_state(hy_batch *b, int i, int kind, const double *host_so
 /* Advance every tube from t = 0 to t_end; asynchronous (one graph launch). */
 hy_status hy_batch_run_to(hy_batch *b, double t_end, double cfl, int solver);
 /* Workgroup size of the batched kernel: 256, 512 or 1024 threads (a tube's
- * cells are dealt round-robin, 24, 12 or 6 register slots per thread); the
- * default is 1024.  The size changes no result.  HY_EINVAL otherwise. */
+ * cells are dealt to the wavefronts in chunks of 56); the default is 1024.
+ * The size changes no result.  HY_EINVAL otherwise. */
 hy_status hy_batch_set_block(hy_batch *b, int threads);
 hy_status hy_batch_get_block(hy_batch *b, int *threads);
 /* Autotuner: runs the whole batch from its current state to t_end with each

@@ -6,7 +6,7 @@
 
 namespace hy {
 
-constexpr int BATCH_NMAX = 6144;  // cells per tube (LDS-resident); up to 6, 12 or 24 per thread
+constexpr int BATCH_NMAX = 6144;  // cells per tube (register-resident)
 
 struct TubeDesc {
     int n;
@@ -23,23 +23,35 @@ struct TubeStatus {
     double t;
 };
 
+// Teams: a long tube may be split over up to TEAM_MAX workgroups, each of
+// which owns a run of its cells.  A queue entry names the tube, how many
+// workgroups may share it, and (for more than one) its team's join word and
+// first mail slot.  Each entry is listed once per workgroup wanted.
+constexpr int TEAM_MAX = 16;
+constexpr int TEAM_SLOTS = 512;   // mail slots of all teams together
+constexpr int TEAM_MIN_CELLS = 128;  // a member's cells at least
+constexpr int MAIL_WORDS = 32;    // per slot and step parity: 12 low-edge values, 12 high-edge values, the rate
+struct BatchItem {
+    int tube, parts, team, slot;
+};
+
 struct BatchCtl {
     unsigned next;  // queue head
-    int solver;
+    int nitems;
     int max_steps;
     int pad;
     double t_end;
     double cfl;
 };
 
-hipError_t launch_batch_reset(BatchCtl *ctl, hipStream_t s);
-// bt = threads per workgroup: 256, 512 or 1024 (4096 / bt cells per thread
-// when the longest tube has at most 4096 cells, else BATCH_NMAX / bt)
+// Clears the queue head, the teams' join words and mail, and the tubes' error flags.
+hipError_t launch_batch_reset(BatchCtl *ctl, unsigned *join, unsigned long long *mail, TubeStatus *status, int ntubes,
+                              hipStream_t s);
+// bt = threads per workgroup: 256, 512 or 1024
 bool batch_bt_supported(int bt);
-hipError_t launch_batch(const TubeDesc *tubes, const int *order, float *U, int64_t ntot, BatchCtl *ctl,
-                        TubeStatus *status, int ntubes, int nmax, int nblocks, int bt, hipStream_t s);
-size_t batch_lds_bytes(int nmax);
-hipError_t prepare_batch(int nmax);
+hipError_t launch_batch(const TubeDesc *tubes, const BatchItem *items, float *U, int64_t ntot, BatchCtl *ctl,
+                        unsigned *join, unsigned long long *mail, TubeStatus *status, int solver, int nmax, int nblocks,
+                        int bt, hipStream_t s);
 int batch_blocks_per_cu(int nmax, int bt);
 
 }  // namespace hy

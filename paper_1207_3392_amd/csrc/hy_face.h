@@ -79,14 +79,18 @@ __device__ __forceinline__ bool to_prim(const T (&u)[ND + 2], T (&w)[ND + 2], T 
 {
     const T ir = rcp_(u[0]);
     w[1] = u[1] * ir;
-    T ke = u[1] * w[1];
+    if constexpr (ND == 1) {
+        w[2] = gm1 * fma_(T(-0.5) * u[1], w[1], u[2]);
+    } else {
+        T ke = u[1] * w[1];
 #pragma unroll
-    for (int d = 1; d < ND; ++d) {
-        w[1 + d] = u[1 + d] * ir;
-        ke = fma_(u[1 + d], w[1 + d], ke);
+        for (int d = 1; d < ND; ++d) {
+            w[1 + d] = u[1 + d] * ir;
+            ke = fma_(u[1 + d], w[1 + d], ke);
+        }
+        w[ND + 1] = gm1 * fma_(T(-0.5), ke, u[ND + 1]);
     }
     w[0] = u[0];
-    w[ND + 1] = gm1 * fma_(T(-0.5), ke, u[ND + 1]);
     return pos_finite(w[0]) & pos_finite(w[ND + 1]);
 }
 
@@ -162,14 +166,20 @@ __device__ __forceinline__ void riemann(const T (&wl)[ND + 2], const T (&wr)[ND 
     const T ap = max3_(T(0), fma_(sg, ul, vl), fma_(sg, ur, vr));
     const T am = max3_(T(0), fma_(sg, ul, -vl), fma_(sg, ur, -vr));
     if constexpr (SOLVER == 0) {
-        T kl = wl[1] * wl[1], kr = wr[1] * wr[1];
+        T El, Er;
+        if constexpr (ND == 1) {
+            El = fma_(vl, T(0.5) * rl * vl, pl * inv_gm1);
+            Er = fma_(vr, T(0.5) * rr * vr, pr * inv_gm1);
+        } else {
+            T kl = wl[1] * wl[1], kr = wr[1] * wr[1];
 #pragma unroll
-        for (int d = 1; d < ND; ++d) {
-            kl = fma_(wl[1 + d], wl[1 + d], kl);
-            kr = fma_(wr[1 + d], wr[1 + d], kr);
+            for (int d = 1; d < ND; ++d) {
+                kl = fma_(wl[1 + d], wl[1 + d], kl);
+                kr = fma_(wr[1 + d], wr[1 + d], kr);
+            }
+            El = fma_(pl, inv_gm1, T(0.5) * rl * kl);
+            Er = fma_(pr, inv_gm1, T(0.5) * rr * kr);
         }
-        const T El = fma_(pl, inv_gm1, T(0.5) * rl * kl);
-        const T Er = fma_(pr, inv_gm1, T(0.5) * rr * kr);
         // F = (a+ F_L + a- F_R - a+ a- (U_R - U_L)) / (a+ + a-).  With the
         // physical flux F = v U + P (P: p in the normal momentum, p v in the
         // energy) each side's state enters once:
@@ -197,7 +207,7 @@ __device__ __forceinline__ void riemann(const T (&wl)[ND + 2], const T (&wr)[ND 
         // (A v_R + B v_L + p_L - p_R) / (A + B), A = rho_R (a+ - v_R), B = rho_L (a- + v_L)
         const T ql = am + vl, qr = ap - vr;
         const T A = rr * qr, B = rl * ql;
-        const T am_ = fma_(A, vr, fma_(B, vl, pl - pr)) * rcp_(A + B);
+        const T am_ = fma_(A, vr, fma_(B, vl, pl - pr)) * rcp_(ND == 1 ? fma_(rr, qr, B) : A + B);
         // eq. FluxHLLC: alpha_- = 0 selects L, then alpha_+ = 0 selects R,
         // then the sign of alpha_m selects the middle state on its side
         const bool sup = (am == T(0)) | (ap == T(0));
@@ -210,10 +220,16 @@ __device__ __forceinline__ void riemann(const T (&wl)[ND + 2], const T (&wr)[ND 
         // supersonic (s_K = 0): a middle speed equal to v_K makes the middle
         // state U_K itself, so the flux below is F_K
         const T sm = sup ? vK : am_;
-        T kk = wk[1] * wk[1];
+        T ek;  // rho v^2 / 2
+        if constexpr (ND == 1) {
+            ek = T(0.5) * rK * vK * vK;
+        } else {
+            T kk = wk[1] * wk[1];
 #pragma unroll
-        for (int d = 1; d < ND; ++d) kk = fma_(wk[1 + d], wk[1 + d], kk);
-        const T EK = fma_(pK, inv_gm1, T(0.5) * rK * kk);
+            for (int d = 1; d < ND; ++d) kk = fma_(wk[1 + d], wk[1 + d], kk);
+            ek = T(0.5) * rK * kk;
+        }
+        const T EK = fma_(pK, inv_gm1, ek);
         // middle state from the jump conditions across the K-side outer wave
         // (s_K - sm is nonzero: opposite signs, or v_K != 0 when supersonic):
         // rho* = rho_K q_K / (s_K - sm), p* = p_K + rho_K q_K (sm - v_K),

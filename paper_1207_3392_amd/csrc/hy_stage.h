@@ -7,6 +7,21 @@
 namespace hy {
 namespace {
 
+// The neighbouring lanes' values: lane l takes l - 1's (lane_dn) or l + 1's
+// (lane_up); the end lane, which no cell that is stored depends on, takes 0.
+__device__ __forceinline__ int dpp_shr(int x) { return __builtin_amdgcn_update_dpp(0, x, 0x138, 0xf, 0xf, true); }
+__device__ __forceinline__ int dpp_shl(int x) { return __builtin_amdgcn_update_dpp(0, x, 0x130, 0xf, 0xf, true); }
+__device__ __forceinline__ float lane_dn(float x) { return __int_as_float(dpp_shr(__float_as_int(x))); }
+__device__ __forceinline__ float lane_up(float x) { return __int_as_float(dpp_shl(__float_as_int(x))); }
+__device__ __forceinline__ double lane_dn(double x)
+{
+    return __hiloint2double(dpp_shr(__double2hiint(x)), dpp_shr(__double2loint(x)));
+}
+__device__ __forceinline__ double lane_up(double x)
+{
+    return __hiloint2double(dpp_shl(__double2hiint(x)), dpp_shl(__double2loint(x)));
+}
+
 // The maximum of x over the lane's row of 16, in every lane of the row (bit
 // patterns of non-negative doubles, which order like the doubles).
 __device__ __forceinline__ unsigned long long row_max(unsigned long long x)

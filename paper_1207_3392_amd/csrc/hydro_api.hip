@@ -12,6 +12,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <limits>
 #include <string>
 #include <vector>
 
@@ -883,15 +884,18 @@ struct hy_batch {
     char *ws = nullptr;
     hy::BatchCtl *ctl = nullptr;
     hy::TubeDesc *tubes = nullptr;
-    int *order = nullptr;
+    hy::BatchItem *items = nullptr;  // the queue: one entry per workgroup wanted, longest first
+    unsigned *join = nullptr;        // teams: members joined so far
+    unsigned long long *mail = nullptr;
     hy::TubeStatus *status = nullptr;
     float *U = nullptr;
     float *W = nullptr;  // scratch for primitive read-back
     hipStream_t stream = nullptr;
     hipStream_t capture = nullptr;
-    hipGraphExec_t exec = nullptr;
+    hipGraphExec_t exec[2] = {nullptr, nullptr};  // per solver (HLL, HLLC)
     int nblocks = 0;
-    int bt = 1024;  // threads per workgroup of the batched kernel
+    int nitems = 0;  // queue entries (set with the order)
+    int bt = 1024;   // threads per workgroup of the batched kernel
     int cus = 1;
     bool order_set = false;
     hipEvent_t ev[2] = {nullptr, nullptr};
@@ -900,10 +904,25 @@ struct hy_batch {
 namespace {
 
 struct BatchLayout {
-    size_t ctl, tubes, order, status, U, W, total;
+    size_t ctl, tubes, items, join, mail, status, U, W, total;
     int64_t ntot;
     int nmax;
 };
+
+// Workgroups of the batched kernel: as many as run at once, at most one per
+// possible queue entry.
+int batch_grid(const hy_batch *b, int bt)
+{
+    return (int)std::min<int64_t>((int64_t)b->count * hy::TEAM_MAX, (int64_t)b->cus * hy::batch_blocks_per_cu(b->nmax, bt));
+}
+
+void batch_drop_graphs(hy_batch *b)
+{
+    for (auto &x : b->exec) {
+        if (x) (void)hipGraphExecDestroy(x);
+        x = nullptr;
+    }
+}
 
 hy_status batch_layout(const hy_patch_desc *descs, int count, BatchLayout *L)
 {
@@ -926,8 +945,12 @@ hy_status batch_layout(const hy_patch_desc *descs, int count, BatchLayout *L)
     o = align_up(o + sizeof(hy::BatchCtl), 256);
     L->tubes = o;
     o = align_up(o + sizeof(hy::TubeDesc) * count, 256);
-    L->order = o;
-    o = align_up(o + sizeof(int) * count, 256);
+    L->items = o;
+    o = align_up(o + sizeof(hy::BatchItem) * hy::TEAM_MAX * (size_t)count, 256);
+    L->join = o;
+    o = align_up(o + sizeof(unsigned) * hy::TEAM_SLOTS, 256);
+    L->mail = o;
+    o = align_up(o + sizeof(unsigned long long) * hy::TEAM_SLOTS * 2 * hy::MAIL_WORDS, 256);
     L->status = o;
     o = align_up(o + sizeof(hy::TubeStatus) * count, 256);
     L->U = o;
@@ -974,7 +997,9 @@ hy_status hy_batch_init(const hy_patch_desc *descs, int count, void *dev_workspa
     b->ws = base;
     b->ctl = (hy::BatchCtl *)(base + L.ctl);
     b->tubes = (hy::TubeDesc *)(base + L.tubes);
-    b->order = (int *)(base + L.order);
+    b->items = (hy::BatchItem *)(base + L.items);
+    b->join = (unsigned *)(base + L.join);
+    b->mail = (unsigned long long *)(base + L.mail);
     b->status = (hy::TubeStatus *)(base + L.status);
     b->U = (float *)(base + L.U);
     b->W = (float *)(base + L.W);
@@ -993,8 +1018,6 @@ hy_status hy_batch_init(const hy_patch_desc *descs, int count, void *dev_workspa
         b->off[i] = o;
         o += d.n[0];
     }
-    std::vector<int> ord(count);
-    std::iota(ord.begin(), ord.end(), 0);
     hy::BatchCtl c{};
     c.max_steps = kBatchMaxSteps;
     // every tube's status starts as "no step taken, no error": the
@@ -1002,12 +1025,10 @@ hy_status hy_batch_init(const hy_patch_desc *descs, int count, void *dev_workspa
     const std::vector<hy::TubeStatus> st0(count, hy::TubeStatus{});
     int dev = 0, cus = 0;
     hipError_t e = hipMemcpyAsync(b->tubes, td.data(), sizeof(hy::TubeDesc) * count, hipMemcpyHostToDevice, b->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(b->order, ord.data(), sizeof(int) * count, hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->status, st0.data(), sizeof(hy::TubeStatus) * count, hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(b->ctl, &c, sizeof(c), hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
-    if (e == hipSuccess) e = hy::prepare_batch(b->nmax);
     if (e == hipSuccess) e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess) e = hipEventCreate(&b->ev[0]);
@@ -1017,7 +1038,7 @@ hy_status hy_batch_init(const hy_patch_desc *descs, int count, void *dev_workspa
         return hip_fail(e, "batch init");
     }
     b->cus = std::max(1, cus);
-    b->nblocks = std::min(count, b->cus * hy::batch_blocks_per_cu(b->nmax, b->bt));
+    b->nblocks = batch_grid(b, b->bt);
     *out = b;
     return HY_OK;
 }
@@ -1060,21 +1081,100 @@ hy_status hy_batch_set_state(hy_batch *b, int i, int kind, const double *host)
     return HY_OK;
 }
 
-// queue order: tubes by descending cost estimate (longest first)
+// The queue: every tube by descending time estimate, the tubes that a team
+// shares first.  A team's members must run together, so all of them stand
+// among the first nblocks entries.  A smaller bound on the longest tube costs
+// more of the machine (a shared step pays for its exchange); of 16 bounds the
+// one whose simulated schedule ends first is taken.  Estimates only: the
+// results do not depend on the split.
 static hy_status batch_order(hy_batch *b)
 {
     if (b->order_set) return HY_OK;
-    std::vector<int> ord(b->count);
+    // us per step, measured: 1.7 (448 cells), 2.4 (896), 4.9 (2048), 8.6 (4096),
+    // 13.5 (6144) on one workgroup; shared, 2.1 to 2.7 for 128 to 512 cells a
+    // member.  Runs by the surcharge of a shared step (512 tubes of 128 .. 4096
+    // cells, 310 of 146 .. 2445): 0.6 us 39.1 / 11.7 ms, 1.0 us 38.5 / 12.5 ms,
+    // 1.5 us 46.1 / 12.5 ms, unshared 78 / 20 ms.
+    auto us = [](double cells, int m) { return std::max(1.75, 0.65 + 2.05e-3 * cells / m) + (m > 1 ? 0.6 : 0.0); };
+    const int n = b->count;
+    std::vector<double> steps(n), est(n), best_est(n);
+    std::vector<int> parts(n), best_parts(n, 1), ord(n);
+    double longest = 0.0;
+    for (int i = 0; i < n; ++i) {
+        steps[i] = b->cost[i] / (double)b->d[i].n[0];
+        longest = std::max(longest, steps[i] * us((double)b->d[i].n[0], 1));
+    }
+    const int room = std::min(b->nblocks, hy::TEAM_SLOTS);
+    double best = std::numeric_limits<double>::infinity();
+    std::vector<double> busy;
+    for (int k = 0; k < 16; ++k) {
+        const double bound = longest * std::pow(0.84, (double)k);  // down to 1/14
+        int shared = 0;
+        for (int i = 0; i < n; ++i) {
+            const double cells = (double)b->d[i].n[0];
+            const int most = (int)std::min<int64_t>(hy::TEAM_MAX, b->d[i].n[0] / hy::TEAM_MIN_CELLS);
+            parts[i] = 1;
+            est[i] = steps[i] * us(cells, 1);
+            for (int m = 2; m <= most && est[i] > bound; ++m) {
+                const double t = steps[i] * us(cells, m);
+                if (t < est[i]) {
+                    parts[i] = m;
+                    est[i] = t;
+                }
+            }
+            if (parts[i] > 1) shared += parts[i];
+        }
+        if (shared > room) break;  // (a smaller bound shares more)
+        std::iota(ord.begin(), ord.end(), 0);
+        std::sort(ord.begin(), ord.end(), [&](int x, int y) { return est[x] != est[y] ? est[x] > est[y] : x < y; });
+        busy.clear();
+        double end = 0.0;
+        for (int i : ord)
+            if (parts[i] > 1) {
+                busy.insert(busy.end(), parts[i], est[i]);
+                end = std::max(end, est[i]);
+            }
+        busy.resize(b->nblocks, 0.0);
+        std::make_heap(busy.begin(), busy.end(), std::greater<double>());
+        for (int i : ord)
+            if (parts[i] == 1) {
+                std::pop_heap(busy.begin(), busy.end(), std::greater<double>());
+                busy.back() += est[i];
+                end = std::max(end, busy.back());
+                std::push_heap(busy.begin(), busy.end(), std::greater<double>());
+            }
+        if (end < best) {
+            best = end;
+            best_parts = parts;
+            best_est = est;
+        }
+    }
     std::iota(ord.begin(), ord.end(), 0);
-    std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) { return b->cost[x] > b->cost[y]; });
-    hipError_t e = hipMemcpyAsync(b->order, ord.data(), sizeof(int) * b->count, hipMemcpyHostToDevice, b->stream);
+    std::sort(ord.begin(), ord.end(), [&](int x, int y) {
+        const bool tx = best_parts[x] > 1, ty = best_parts[y] > 1;
+        if (tx != ty) return tx;
+        return best_est[x] != best_est[y] ? best_est[x] > best_est[y] : x < y;
+    });
+    std::vector<hy::BatchItem> items;
+    int team = 0, slot = 0;
+    for (int i : ord) {
+        const int m = best_parts[i];
+        for (int k = 0; k < m; ++k) items.push_back({i, m, m > 1 ? team : -1, m > 1 ? slot : -1});
+        if (m > 1) {
+            ++team;
+            slot += m;
+        }
+    }
+    b->nitems = (int)items.size();
+    hipError_t e = hipMemcpyAsync(b->items, items.data(), sizeof(hy::BatchItem) * items.size(), hipMemcpyHostToDevice,
+                                  b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     if (e != hipSuccess) return hip_fail(e, "queue order upload");
     b->order_set = true;
     return HY_OK;
 }
 
-static hy_status batch_capture(hy_batch *b)
+static hy_status batch_capture(hy_batch *b, int solver)
 {
     hipError_t e = hipSuccess;
     if (!b->capture) e = hipStreamCreateWithFlags(&b->capture, hipStreamNonBlocking);
@@ -1082,13 +1182,13 @@ static hy_status batch_capture(hy_batch *b)
     hipGraph_t g = nullptr;
     e = hipStreamBeginCapture(b->capture, hipStreamCaptureModeRelaxed);
     if (e != hipSuccess) return hip_fail(e, "begin capture");
-    hipError_t e1 = hy::launch_batch_reset(b->ctl, b->capture);
-    hipError_t e2 = hy::launch_batch(b->tubes, b->order, b->U, b->ntot, b->ctl, b->status, b->count, b->nmax,
-                                     b->nblocks, b->bt, b->capture);
+    hipError_t e1 = hy::launch_batch_reset(b->ctl, b->join, b->mail, b->status, b->count, b->capture);
+    hipError_t e2 = hy::launch_batch(b->tubes, b->items, b->U, b->ntot, b->ctl, b->join, b->mail, b->status, solver,
+                                     b->nmax, b->nblocks, b->bt, b->capture);
     e = hipStreamEndCapture(b->capture, &g);
     if (e1 != hipSuccess) e = e1;
     if (e2 != hipSuccess) e = e2;
-    if (e == hipSuccess) e = hipGraphInstantiate(&b->exec, g, nullptr, nullptr, 0);
+    if (e == hipSuccess) e = hipGraphInstantiate(&b->exec[solver], g, nullptr, nullptr, 0);
     if (g) hipGraphDestroy(g);
     if (e != hipSuccess) return hip_fail(e, "graph capture");
     return HY_OK;
@@ -1103,18 +1203,19 @@ hy_status hy_batch_run_to(hy_batch *b, double t_end, double cfl, int solver)
     hy_status st0 = batch_order(b);
     if (st0 != HY_OK) return st0;
     hipError_t e = hipSuccess;
-    if (!b->exec) {
-        hy_status st = batch_capture(b);
+    const int sv = solver == HY_HLL ? HY_HLL : HY_HLLC;  // no transverse faces in 1D: the switch is HLLC
+    if (!b->exec[sv]) {
+        hy_status st = batch_capture(b, sv);
         if (st != HY_OK) return st;
     }
     hy::BatchCtl c{};
-    c.solver = solver == HY_HLLC_SWITCH ? HY_HLLC : solver;  // no transverse faces in 1D
     c.max_steps = kBatchMaxSteps;
+    c.nitems = b->nitems;
     c.t_end = t_end;
     c.cfl = cfl;
     e = hipMemcpyAsync(b->ctl, &c, sizeof(c), hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess) e = hipEventRecord(b->ev[0], b->stream);
-    if (e == hipSuccess) e = hipGraphLaunch(b->exec, b->stream);
+    if (e == hipSuccess) e = hipGraphLaunch(b->exec[sv], b->stream);
     if (e == hipSuccess) e = hipEventRecord(b->ev[1], b->stream);
     if (e != hipSuccess) return hip_fail(e, "batch launch");
     return HY_OK;
@@ -1129,8 +1230,8 @@ hy_status hy_batch_autotune(hy_batch *b, double t_end, double cfl, int solver, i
     hy_status st = batch_order(b);
     if (st != HY_OK) return st;
     hy::BatchCtl c{};
-    c.solver = solver == HY_HLLC_SWITCH ? HY_HLLC : solver;  // no transverse faces in 1D
     c.max_steps = kBatchMaxSteps;
+    c.nitems = b->nitems;
     c.t_end = t_end;
     c.cfl = cfl;
     const size_t ubytes = sizeof(float) * 3 * (size_t)b->ntot;
@@ -1145,13 +1246,13 @@ hy_status hy_batch_autotune(hy_batch *b, double t_end, double cfl, int solver, i
     for (int bt : {1024, 512, 256})
         if (bt != b->bt) bts.push_back(bt);
     for (int bt : bts) {
-        const int nb = std::min(b->count, b->cus * hy::batch_blocks_per_cu(b->nmax, bt));
+        const int nb = batch_grid(b, bt);
         if (e == hipSuccess) e = hipMemcpyAsync(b->U, b->W, ubytes, hipMemcpyDeviceToDevice, b->stream);
-        if (e == hipSuccess) e = hy::launch_batch_reset(b->ctl, b->stream);
+        if (e == hipSuccess) e = hy::launch_batch_reset(b->ctl, b->join, b->mail, b->status, b->count, b->stream);
         if (e == hipSuccess) e = hipEventRecord(b->ev[0], b->stream);
         if (e == hipSuccess)
-            e = hy::launch_batch(b->tubes, b->order, b->U, b->ntot, b->ctl, b->status, b->count, b->nmax, nb, bt,
-                                 b->stream);
+            e = hy::launch_batch(b->tubes, b->items, b->U, b->ntot, b->ctl, b->join, b->mail, b->status,
+                                 solver == HY_HLL ? HY_HLL : HY_HLLC, b->nmax, nb, bt, b->stream);
         if (e == hipSuccess) e = hipEventRecord(b->ev[1], b->stream);
         if (e == hipSuccess) e = hipEventSynchronize(b->ev[1]);
         float ms = 0.f;
@@ -1168,11 +1269,9 @@ hy_status hy_batch_autotune(hy_batch *b, double t_end, double cfl, int solver, i
     if (e != hipSuccess) return hip_fail(e, "batch autotune");
     if (bbt != b->bt) {
         b->bt = bbt;
-        b->nblocks = std::min(b->count, b->cus * hy::batch_blocks_per_cu(b->nmax, bbt));
-        if (b->exec) {  // recaptured with the new workgroup size at the next run
-            hipGraphExecDestroy(b->exec);
-            b->exec = nullptr;
-        }
+        b->nblocks = batch_grid(b, bbt);
+        b->order_set = false;  // (the split depends on how many workgroups run at once)
+        batch_drop_graphs(b);  // recaptured with the new workgroup size at the next run
     }
     if (best_bt) *best_bt = bbt;
     if (best_ms) *best_ms = bms;
@@ -1185,12 +1284,12 @@ hy_status hy_batch_set_block(hy_batch *b, int bt)
     if (!hy::batch_bt_supported(bt)) return fail(HY_EINVAL, "workgroup size must be 256, 512 or 1024");
     if (bt != b->bt) {
         b->bt = bt;
-        b->nblocks = std::min(b->count, b->cus * hy::batch_blocks_per_cu(b->nmax, bt));
-        if (b->exec) {
+        b->nblocks = batch_grid(b, bt);
+        b->order_set = false;  // (the split depends on how many workgroups run at once)
+        if (b->exec[0] || b->exec[1]) {
             hipError_t e = hipStreamSynchronize(b->stream);
             if (e != hipSuccess) return hip_fail(e, "batch sync");
-            hipGraphExecDestroy(b->exec);
-            b->exec = nullptr;
+            batch_drop_graphs(b);
         }
     }
     return HY_OK;
@@ -1257,7 +1356,7 @@ hy_status hy_batch_destroy(hy_batch *b)
 {
     if (!b) return HY_OK;
     hipStreamSynchronize(b->stream);
-    if (b->exec) hipGraphExecDestroy(b->exec);
+    batch_drop_graphs(b);
     if (b->capture) hipStreamDestroy(b->capture);
     for (auto &ev : b->ev)
         if (ev) hipEventDestroy(ev);
