@@ -76,3 +76,63 @@ def test_shared_tubes_equal_unshared(bc):
         one.close()
         many.close()
 
+
+def patch_case(n, bc, solver, prec, steps, accel=0.0, check=True):
+    pr = tube(n, bc, 3 * n + prec)
+    pr.accel = (accel, 0.0, 0.0)
+    d = oracle.Desc.from_problem(pr, solver=solver)
+    p = hydro.Patch(pr, precision=prec)
+    U = p.get_state(hydro.CONSERVED)
+    dts = []
+    for _ in range(steps):
+        dts.append(oracle.cfl_dt(d, U, 0.4))
+        U = oracle.step(d, U, dts[-1])
+    s = np.max(np.abs(U), axis=1, keepdims=True)
+    s[1] = max(s[1, 0], np.sqrt(2 * s[0, 0] * s[2, 0]))
+    tol = 1e-12 if prec == 64 else 2e-5
+    p.advance(steps, 0.4, solver=solver)  # dt from the device
+    assert np.max(np.abs(p.get_state(hydro.CONSERVED) - U) / s) < tol, (n, bc, solver)
+    assert abs(p.time() - sum(dts)) <= (1e-13 if prec == 64 else 2e-6) * sum(dts)
+    nxt = oracle.cfl_dt(d, U, 0.4)
+    assert abs(p.cfl_dt(0.4) - nxt) <= (1e-12 if prec == 64 else 2e-6) * nxt
+    p.step(nxt, solver)  # dt from the host
+    assert np.max(np.abs(p.get_state(hydro.CONSERVED) - oracle.step(d, U, nxt)) / s) < tol, (n, bc, solver)
+    p.close()
+
+
+@pytest.mark.parametrize("prec", [32, 64])
+@pytest.mark.parametrize("solver", [hydro.HLL, hydro.HLLC])
+def test_patches_at_chunk_edges(prec, solver):
+    for n in (2, 3, 55, 56, 57, 60, 113, 897):
+        for k, bc in enumerate(KINDS + ((1, 2),)):
+            patch_case(n, bc, solver, prec, 3, accel=0.1 * k)
+
+
+@pytest.mark.parametrize("prec", [32, 64])
+def test_patches_around_the_longest_line(prec):
+    """The longest line and one cell more (which takes the stage kernels)."""
+    n = 5376 if prec == 32 else 3584
+    for k in (0, 1):
+        patch_case(n + k, wl.BC_REFLECT, hydro.HLLC, prec, 2)
+
+
+def test_runs_longer_than_a_launch():
+    """5001 steps in one call (more than one launch, an odd count) equal the
+    same steps in several calls and as a graph; t_end stops the clock."""
+    pr = tube(40, wl.BC_PERIODIC, 5)
+    a, b, c = hydro.Patch(pr), hydro.Patch(pr), hydro.Patch(pr)
+    a.advance(5001, 0.4)
+    for k in (1, 2000, 2999, 1):
+        b.advance(k, 0.4)
+    c.advance_graph(5001, 0.4)
+    assert np.array_equal(a.get_state(), b.get_state()) and a.time() == b.time()
+    assert np.array_equal(a.get_state(), c.get_state()) and a.time() == c.time()
+    assert a.cfl_dt(0.4) == b.cfl_dt(0.4) == c.cfl_dt(0.4)
+    end = a.time() + 2.5 * a.cfl_dt(0.4)
+    a.advance(7, 0.4, end)
+    assert a.time() == pytest.approx(end, rel=1e-14)
+    u = a.get_state()
+    a.advance(3, 0.4, end)
+    assert np.array_equal(u, a.get_state()) and a.time() == pytest.approx(end, rel=1e-14)
+    for p in (a, b, c):
+        p.close()
