@@ -47,6 +47,11 @@ struct BatchCtl {
 // Clears the queue head, the teams' join words and mail, and the tubes' error flags.
 hipError_t launch_batch_reset(BatchCtl *ctl, unsigned *join, unsigned long long *mail, TubeStatus *status, int ntubes,
                               hipStream_t s);
+// One tube's state (U: its first cell) from and to pinned host memory
+// (3 x n floats), primitives converted on the way; get also fetches its status.
+hipError_t launch_tube_put(const float *host, float *U, int64_t ntot, int n, bool prim, float inv_gm1, hipStream_t s);
+hipError_t launch_tube_get(const float *U, int64_t ntot, int n, bool prim, float gm1, const TubeStatus *st, float *host,
+                           TubeStatus *hst, hipStream_t s);
 // bt = threads per workgroup: 256, 512 or 1024
 bool batch_bt_supported(int bt);
 hipError_t launch_batch(const TubeDesc *tubes, const BatchItem *items, float *U, int64_t ntot, BatchCtl *ctl,

@@ -922,6 +922,10 @@ struct hy_batch {
     int cus = 1;
     bool order_set = false;
     hipEvent_t ev[2] = {nullptr, nullptr};
+    // pinned staging: every tube's state (3 x n floats at 3 off[i]), then one status
+    float *stage = nullptr;
+    hy::TubeStatus *stage_status = nullptr;
+    std::vector<char> uploading;  // tube i's staging may still be read by its upload
 };
 
 namespace {
@@ -1056,10 +1060,17 @@ hy_status hy_batch_init(const hy_patch_desc *descs, int count, void *dev_workspa
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess) e = hipEventCreate(&b->ev[0]);
     if (e == hipSuccess) e = hipEventCreate(&b->ev[1]);
+    if (e == hipSuccess)
+        e = hipHostMalloc((void **)&b->stage, align_up(sizeof(float) * 3 * (size_t)b->ntot, 64) + sizeof(hy::TubeStatus),
+                          hipHostMallocDefault);
     if (e != hipSuccess) {
+        for (auto &ev : b->ev)
+            if (ev) (void)hipEventDestroy(ev);
         delete b;
         return hip_fail(e, "batch init");
     }
+    b->stage_status = (hy::TubeStatus *)((char *)b->stage + align_up(sizeof(float) * 3 * (size_t)b->ntot, 64));
+    b->uploading.assign(count, 0);
     b->cus = std::max(1, cus);
     b->nblocks = batch_grid(b, b->bt);
     *out = b;
@@ -1072,33 +1083,39 @@ hy_status hy_batch_set_state(hy_batch *b, int i, int kind, const double *host)
     if (i < 0 || i >= b->count) return fail(HY_EINVAL, "tube index out of range");
     if (kind != HY_PRIMITIVE && kind != HY_CONSERVED) return fail(HY_EINVAL, "unknown state kind");
     const int64_t n = b->d[i].n[0];
-    std::vector<float> st(3 * n);
-    for (int64_t k = 0; k < 3 * n; ++k) st[k] = (float)host[k];
     hipError_t e = hipSuccess;
-    for (int v = 0; v < 3 && e == hipSuccess; ++v)
-        e = hipMemcpyAsync(b->U + v * b->ntot + b->off[i], st.data() + v * n, sizeof(float) * n, hipMemcpyHostToDevice,
-                           b->stream);
-    if (e == hipSuccess && kind == HY_PRIMITIVE) {
-        const double gm1 = b->d[i].gamma - 1.0;
-        e = hy::launch_prim_to_cons<float>(b->U + b->off[i], n, b->ntot, 1, (float)gm1, (float)(1.0 / gm1), b->stream);
+    if (b->uploading[i]) {  // (set twice in a row: the first upload must have been read)
+        e = hipStreamSynchronize(b->stream);
+        std::fill(b->uploading.begin(), b->uploading.end(), 0);
     }
-    if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     if (e != hipSuccess) return hip_fail(e, "tube upload");
+    float *st = b->stage + 3 * b->off[i];
+    for (int64_t k = 0; k < 3 * n; ++k) st[k] = (float)host[k];
+    e = hy::launch_tube_put(st, b->U + b->off[i], b->ntot, (int)n, kind == HY_PRIMITIVE,
+                            (float)(1.0 / (b->d[i].gamma - 1.0)), b->stream);
+    if (e != hipSuccess) return hip_fail(e, "tube upload");
+    b->uploading[i] = 1;
     // scheduling estimate only: tube length times the cells a signal crosses
-    // per unit time, n (|v| + c) / L, from the input primitives or conserved
-    // variables (the kernel recomputes everything it uses)
-    double smax = 0.0;
-    const double g = b->d[i].gamma;
-    for (int64_t k = 0; k < n; ++k) {
-        double rho, v, p;
-        if (kind == HY_PRIMITIVE) {
-            rho = host[k]; v = host[n + k]; p = host[2 * n + k];
-        } else {
-            rho = host[k]; v = host[n + k] / rho; p = (g - 1.0) * (host[2 * n + k] - 0.5 * host[n + k] * v);
+    // per unit time, n (|v| + c) / L, from the input (the kernel recomputes
+    // everything it uses); eight running maxima so the loop vectorises
+    const float g = (float)b->d[i].gamma;
+    float top[8] = {};
+    auto speed = [&](float rho, float x, float y) {
+        const float v = kind == HY_PRIMITIVE ? x : x / rho;
+        const float c2 = kind == HY_PRIMITIVE ? g * y / rho : g * (g - 1.0f) * (y / rho - 0.5f * v * v);
+        return std::fabs(v) + std::sqrt(c2 > 0.0f ? c2 : 0.0f);
+    };
+    int64_t k = 0;
+    for (; k + 8 <= n; k += 8)
+        for (int j = 0; j < 8; ++j) {
+            const float s = speed(st[k + j], st[n + k + j], st[2 * n + k + j]);
+            top[j] = s > top[j] && s <= std::numeric_limits<float>::max() ? s : top[j];
         }
-        const double s = std::fabs(v) + std::sqrt(std::max(g * p / rho, 0.0));
-        if (std::isfinite(s)) smax = std::max(smax, s);
+    for (; k < n; ++k) {
+        const float s = speed(st[k], st[n + k], st[2 * n + k]);
+        if (s > top[0] && s <= std::numeric_limits<float>::max()) top[0] = s;
     }
+    const double smax = *std::max_element(top, top + 8);
     b->cost[i] = (double)n * (double)n * smax / (b->d[i].hi[0] - b->d[i].lo[0]);
     b->order_set = false;
     return HY_OK;
@@ -1342,20 +1359,14 @@ hy_status hy_batch_get_state(hy_batch *b, int i, int kind, double *out)
     if (i < 0 || i >= b->count) return fail(HY_EINVAL, "tube index out of range");
     if (kind != HY_PRIMITIVE && kind != HY_CONSERVED) return fail(HY_EINVAL, "unknown state kind");
     const int64_t n = b->d[i].n[0];
-    const float *src = b->U + b->off[i];
-    hipError_t e = hipSuccess;
-    if (kind == HY_PRIMITIVE) {
-        e = hy::launch_cons_to_prim<float>(src, b->W + b->off[i], n, b->ntot, 1, (float)(b->d[i].gamma - 1.0), b->stream);
-        src = b->W + b->off[i];
-    }
-    std::vector<float> st(3 * n);
-    for (int v = 0; v < 3 && e == hipSuccess; ++v)
-        e = hipMemcpyAsync(st.data() + v * n, src + v * b->ntot, sizeof(float) * n, hipMemcpyDeviceToHost, b->stream);
-    hy::TubeStatus ts{};
-    if (e == hipSuccess) e = hipMemcpyAsync(&ts, b->status + i, sizeof(ts), hipMemcpyDeviceToHost, b->stream);
+    float *st = b->stage + 3 * b->off[i];
+    hipError_t e = hy::launch_tube_get(b->U + b->off[i], b->ntot, (int)n, kind == HY_PRIMITIVE,
+                                       (float)(b->d[i].gamma - 1.0), b->status + i, st, b->stage_status, b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     if (e != hipSuccess) return hip_fail(e, "tube download");
+    std::fill(b->uploading.begin(), b->uploading.end(), 0);
     for (int64_t k = 0; k < 3 * n; ++k) out[k] = st[k];
+    const hy::TubeStatus ts = *b->stage_status;
     if (ts.err & 1) return fail(HY_ESTATE, "a kernel met rho <= 0, p <= 0 or a non-finite value in this tube");
     return HY_OK;
 }
@@ -1383,6 +1394,7 @@ hy_status hy_batch_destroy(hy_batch *b)
     if (b->capture) hipStreamDestroy(b->capture);
     for (auto &ev : b->ev)
         if (ev) hipEventDestroy(ev);
+    if (b->stage) (void)hipHostFree(b->stage);
     delete b;
     return HY_OK;
 }
