@@ -8,7 +8,8 @@
 
 namespace hy {
 
-constexpr int TRAIN_BLOCKS = 256;
+constexpr int TRAIN_BLOCKS = 256;  // partial rows at most
+constexpr int TRAIN_WAVES = 4;     // wavefronts per workgroup of the gradient kernel
 
 // The static staging array of the allocation-free sample entry point: bytes
 // per GPU, and the devices it serves.

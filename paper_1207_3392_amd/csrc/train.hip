@@ -9,12 +9,11 @@
 // coarse cell, slope 0.4 (-3 w1 - w2 + w3 + 3 w4)), clamped to the TVD
 // region and divided by the same normalisation s.
 //
-// Step: each workgroup takes tiles of 64 samples and runs the network forward
-// and backward with v_mfma_f32_16x16x16_bf16 on operands staged in LDS
-// (weights and activations in bfloat16, accumulation in FP32), accumulating
-// its share of the gradient of the mean squared error in FP32; a second
-// kernel adds the workgroup partials in a fixed order and a third applies
-// Adam to the FP32 master weights.
+// Step: each wavefront takes tiles of 64 samples and runs the network forward
+// and backward on the matrix cores (weights and activations in bfloat16,
+// accumulation in FP32), accumulating its share of the gradient of the mean
+// squared error in FP32; a second kernel adds the workgroup partials in a
+// fixed order and applies Adam to the FP32 master weights.
 #include "hy_internal.h"
 #include "hy_mlp.h"
 #include "hy_train.h"
@@ -29,14 +28,6 @@ namespace {
 
 typedef short s4 __attribute__((ext_vector_type(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ unsigned short bfu(float x)
-{
-    __hip_bfloat16 b = __float2bfloat16(x);
-    unsigned short u;
-    __builtin_memcpy(&u, &b, 2);
-    return u;
-}
 
 // ------------------------------------------------------------ data ----
 
@@ -142,342 +133,308 @@ __global__ void __launch_bounds__(256) k_samples(const float *__restrict__ Wc, c
 
 // ------------------------------------------------------------ step ----
 
-constexpr int TW = 4;          // waves per workgroup
 constexpr int TS = 64;         // samples per wave tile
 constexpr int H = MLP_H;       // 32
-constexpr int KI = 16;         // layer-1 K, padded from 4
 
-// A fragment of a 16 x 16 block: lane (grp, col) holds element
-// (i0 + col, j0 + 4 grp + jj), jj = 0..3, of a bf16 matrix at base[i * si + j * sj]
-__device__ __forceinline__ s4 frag(const unsigned short *base, int si, int sj, int i0, int j0, int grp, int col)
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+typedef __bf16 b8 __attribute__((ext_vector_type(8)));
+typedef unsigned u2 __attribute__((ext_vector_type(2)));
+typedef unsigned u4 __attribute__((ext_vector_type(4)));
+
+// two floats to bfloat16 (round to nearest even), the first in the low half
+__device__ __forceinline__ unsigned pk(float a, float b)
 {
-    s4 r;
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj) r[jj] = (short)base[(i0 + col) * si + (j0 + 4 * grp + jj) * sj];
-    return r;
+    return __builtin_bit_cast(unsigned, __builtin_convertvector((f2){a, b}, b2));
+}
+__device__ __forceinline__ u2 pk4(const f4 v) { return (u2){pk(v[0], v[1]), pk(v[2], v[3])}; }
+__device__ __forceinline__ u2 pk4_relu(const f4 v)
+{
+    return (u2){pk(fmaxf(v[0], 0.f), fmaxf(v[1], 0.f)), pk(fmaxf(v[2], 0.f), fmaxf(v[3], 0.f))};
+}
+__device__ __forceinline__ b8 op8(const u2 lo, const u2 hi)
+{
+    return __builtin_bit_cast(b8, (u4){lo[0], lo[1], hi[0], hi[1]});
 }
 
 // x rounded to the nearest bfloat16 (ties to even), as a float: the third
 // layer's operands, which the inference kernel feeds to the matrix cores
 __device__ __forceinline__ float bfr(float x) { return __bfloat162float(__float2bfloat16(x)); }
 
-__device__ __forceinline__ f4 mfma(s4 a, s4 b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ f4 mfma16(u2 a, u2 b, f4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s4, a), __builtin_bit_cast(s4, b), c, 0, 0, 0);
+}
+__device__ __forceinline__ f4 mfma32(b8 a, b8 b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ f4 splat(float x) { return (f4){x, x, x, x}; }
 
-// Per-wave LDS: X (64 x 16), H1 (64 x 32), dZ (64 x 32), all bf16.
-struct WaveLds {
-    unsigned short X[TS * KI];
-    unsigned short H1[TS * H];
-    unsigned short dZ[TS * H];
-    float Z1[TS * H];
-    float dy[TS];
-};
+// The gradient of the mean squared error over the batch: per-workgroup partial
+// sums.  A wave takes 64 samples, lane (grp = lane / 16, col = lane % 16)
+// owning sample 16 grp + col.  Every layer is evaluated twice on the matrix
+// cores, with the operands swapped: once with the units along the result's
+// rows (a lane holds 4 units of one sample: what the next layer and the
+// backward product through W2 take as an operand) and once with the samples
+// along the rows (a lane holds 4 samples of one unit: what the weight
+// gradients, contractions over the samples, take as operands).  So nothing is
+// transposed, activations stay in registers, and only the samples and targets
+// go through LDS, within the wavefront.  K = 32 operands: K index 8 grp + jj
+// stands for unit 4 grp + jj (jj < 4) or 16 + 4 grp + jj - 4, and in the
+// weight gradients for those samples of two 16-sample batches.
+//
+// What bounds it: the latency of one wavefront's chain (gather, 64 matrix
+// instructions, about 600 vector ones) under the weights' load, one tile per
+// wavefront up to 65,536 samples, so four wavefronts per workgroup and as many
+// workgroups as there are rows of partial sums.  65,536 samples: 18.3 -> 10.0 us
+// per launch against operands staged element by element in LDS between seven
+// workgroup barriers; a step with the sum below 23.5 -> 11.0 us.
+constexpr int TW = TRAIN_WAVES;
 
 __global__ void __launch_bounds__(64 * TW) k_train_grad(const MlpDevice *__restrict__ m, const float *__restrict__ x,
                                                         const float *__restrict__ t, const int *__restrict__ idx,
                                                         int64_t batch, float inv_batch, float *__restrict__ partial,
                                                         float *__restrict__ loss_partial)
 {
-    __shared__ unsigned short sW1[H * KI];  // W1 as (j, k), k padded
-    __shared__ unsigned short sW2[H * H];   // W2 as (j, k)
-    __shared__ WaveLds wl[TW];
     __shared__ float sg[TW][MLP_NPARAM + 3];
-
+    __shared__ __align__(16) unsigned short sX[TW][MLP_IN][TS];  // the tile's inputs, bf16
+    __shared__ __align__(16) float sT[TW][TS];     // and targets
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, grp = lane >> 4, col = lane & 15;
-    for (int i = threadIdx.x; i < H * KI; i += 64 * TW) {
-        const int j = i / KI, k = i % KI;
-        sW1[i] = k < MLP_IN ? bfu(m->w1[j][k]) : 0;
-    }
-    for (int i = threadIdx.x; i < H * H; i += 64 * TW) sW2[i] = bfu(m->w2[i / H][i % H]);
-    for (int i = lane; i < MLP_NPARAM + 3; i += 64) sg[wv][i] = 0.f;
-    __syncthreads();
-
-    WaveLds &L = wl[wv];
-    float lsum = 0.f;
-    // every wave runs the same number of tile iterations (tiles past the end
-    // are empty), so workgroup barriers can order the per-wave LDS traffic
     const int64_t ntile = (batch + TS - 1) / TS;
-    const int64_t iters = (ntile + (int64_t)gridDim.x * TW - 1) / ((int64_t)gridDim.x * TW);
-    for (int64_t it = 0; it < iters; ++it) {
-        const int64_t tile = (it * gridDim.x + blockIdx.x) * TW + wv;
-        // ---- stage the sample tile ----
-        const int64_t si = tile * TS + lane;
-        const bool valid = si < batch;
-        const int64_t s = valid ? (int64_t)idx[si] : 0;
-        float xs[MLP_IN];
-#pragma unroll
-        for (int k = 0; k < MLP_IN; ++k) xs[k] = valid ? x[s * 4 + k] : 0.f;
-        const float ts = valid ? t[s] : 0.f;
-#pragma unroll
-        for (int k = 0; k < KI; ++k) L.X[lane * KI + k] = k < MLP_IN ? bfu(xs[k]) : 0;
-        __syncthreads();
-
-        // ---- layer 1: Z1 (64 x 32) = X (64 x 16) W1^T + b1 ----
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb) {
-                f4 c;
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) c[jj] = m->b1[16 * nb + col];
-                // D[m][n] = sum_k X[m][k] W1[n][k]: A = X (m, k), B(k, n) = W1[n][k]
-                const s4 a = frag(L.X, KI, 1, 16 * mb, 0, grp, col);
-                s4 b;
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) b[jj] = (short)sW1[(16 * nb + col) * KI + 4 * grp + jj];
-                // fix the accumulator layout: C[m = 4 grp + jj][n = col] = b1[n]
-                const f4 d = mfma(a, b, c);
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) {
-                    const int mrow = 16 * mb + 4 * grp + jj, ncol = 16 * nb + col;
-                    L.Z1[mrow * H + ncol] = d[jj];
-                    L.H1[mrow * H + ncol] = bfu(fmaxf(d[jj], 0.f));
-                }
-            }
-        __syncthreads();
-
-        // ---- layer 2 and 3: Z2 = H1 W2^T + b2; y = w3 . relu(Z2) + b3 ----
-        float z2[4][2][4];
-        float ypart[4][4];
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb) {
-#pragma unroll
-            for (int jj = 0; jj < 4; ++jj) ypart[mb][jj] = 0.f;
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb) {
-                f4 c;
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) c[jj] = m->b2[16 * nb + col];
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb) {
-                    const s4 a = frag(L.H1, H, 1, 16 * mb, 16 * kb, grp, col);
-                    s4 b;
-#pragma unroll
-                    for (int jj = 0; jj < 4; ++jj) b[jj] = (short)sW2[(16 * nb + col) * H + 16 * kb + 4 * grp + jj];
-                    c = mfma(a, b, c);
-                }
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) {
-                    z2[mb][nb][jj] = c[jj];
-                    ypart[mb][jj] += bfr(m->w3[16 * nb + col]) * bfr(fmaxf(c[jj], 0.f));
-                }
-            }
+    float xs[MLP_IN], ts;
+    auto gather = [&](int64_t si) {
+        xs[0] = xs[1] = xs[2] = xs[3] = ts = 0.f;
+        if (si < batch) {
+            const int64_t s = (int64_t)idx[si];
+            __builtin_memcpy(xs, x + s * 4, sizeof(xs));
+            ts = t[s];
         }
-        // y for sample row r = 16 mb + 4 grp + jj: sum over the 16 lanes of the row group
+    };
+    int64_t tile = (int64_t)blockIdx.x * TW + wv;
+    gather(tile * TS + lane);  // two dependent fetches, under way while the weights arrive
+
+    // the network as this lane's operands
+    u2 w1v[2];
+    b8 a2[2], a2t[2], a3;
+    f4 c1[2], c2[2], w3a[2];
+    float c1t[2], c2t[2], w3b[2];
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
+    for (int mb = 0; mb < 2; ++mb) {
+        const float *r = m->w1[16 * mb + col];
+        w1v[mb] = (u2){pk(r[0], r[1]), pk(r[2], r[3])};
+        const float *w = m->w2[16 * mb + col];
+        a2[mb] = op8((u2){pk(w[4 * grp], w[4 * grp + 1]), pk(w[4 * grp + 2], w[4 * grp + 3])},
+                     (u2){pk(w[16 + 4 * grp], w[17 + 4 * grp]), pk(w[18 + 4 * grp], w[19 + 4 * grp])});
+        f4 lo, hi;
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+            lo[jj] = m->w2[4 * grp + jj][16 * mb + col];
+            hi[jj] = m->w2[16 + 4 * grp + jj][16 * mb + col];
+            c1[mb][jj] = m->b1[16 * mb + 4 * grp + jj];
+            c2[mb][jj] = m->b2[16 * mb + 4 * grp + jj];
+            w3a[mb][jj] = bfr(m->w3[16 * mb + 4 * grp + jj]);
+        }
+        a2t[mb] = op8(pk4(lo), pk4(hi));
+        c1t[mb] = m->b1[16 * mb + col];
+        c2t[mb] = m->b2[16 * mb + col];
+        w3b[mb] = bfr(m->w3[16 * mb + col]);
+    }
+    a3 = op8(pk4(w3a[0]), pk4(w3a[1]));  // (already bf16 values)
+    const float b3 = m->b3;
+
+    f4 gW2[2][2] = {}, gW1[2] = {};
+    float gb1[2] = {}, gb2[2] = {}, gw3[2] = {}, gb3 = 0.f, lsum = 0.f;
+    for (; tile < ntile; tile += (int64_t)gridDim.x * TW) {
+        const int nvalid = batch - tile * TS < TS ? (int)(batch - tile * TS) : TS;
+        const u2 xb = {pk(xs[0], xs[1]), pk(xs[2], xs[3])};
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // (the last tile's reads)
+        sX[wv][0][lane] = (unsigned short)xb[0];
+        sX[wv][1][lane] = (unsigned short)(xb[0] >> 16);
+        sX[wv][2][lane] = (unsigned short)xb[1];
+        sX[wv][3][lane] = (unsigned short)(xb[1] >> 16);
+        sT[wv][lane] = ts;
+        gather((tile + (int64_t)gridDim.x * TW) * TS + lane);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+
+        b8 dz2s[4];              // dZ2, 4 units of a sample: backward operand
+        u2 h1p[4][2], dz2p[4][2], dz1p[4][2];  // H1, dZ2, dZ1, 4 samples of a unit: gradient operands
+        f4 e1[4][2];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            u2 a1[2];
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb) a1[mb] = grp == g ? w1v[mb] : (u2){0u, 0u};
+            const b8 h1 = op8(pk4_relu(mfma16(a1[0], xb, c1[0])), pk4_relu(mfma16(a1[1], xb, c1[1])));
+            f4 d2[2], e2[2];
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb) {
+                e1[g][mb] = mfma16(xb, a1[mb], splat(c1t[mb]));
+                d2[mb] = mfma32(a2[mb], h1, c2[mb]);
+                e2[mb] = mfma32(h1, a2[mb], splat(c2t[mb]));
+                h1p[g][mb] = pk4_relu(e1[g][mb]);
+            }
+            const b8 h2 = op8(pk4_relu(d2[0]), pk4_relu(d2[1]));
+            const float y1 = mfma32(a3, h2, splat(b3))[0];  // sample 16 g + col
+            const f4 y2 = mfma32(h2, a3, splat(b3));        // samples 16 g + 4 grp + jj
+            const float r1 = 16 * g + col < nvalid ? y1 - sT[wv][16 * g + col] : 0.f;
+            if (grp == g) lsum += r1 * r1;
+            const float dy1 = 2.f * r1 * inv_batch;
+            const f4 t2 = *(const f4 *)&sT[wv][16 * g + 4 * grp];
+            f4 dy2;
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
-                float v = ypart[mb][jj];
-                v += __shfl_xor(v, 1, 64);
-                v += __shfl_xor(v, 2, 64);
-                v += __shfl_xor(v, 4, 64);
-                v += __shfl_xor(v, 8, 64);
-                ypart[mb][jj] = v + m->b3;
+                dy2[jj] = 16 * g + 4 * grp + jj < nvalid ? 2.f * (y2[jj] - t2[jj]) * inv_batch : 0.f;
+                gb3 += dy2[jj];
             }
-        // residual of this lane's own sample (row = lane): held by the lanes of
-        // row group (lane / 4) % 4 in block lane / 16
-        {
-            float yown = 0.f;
+            f4 q[2];
 #pragma unroll
-            for (int mb = 0; mb < 4; ++mb)
+            for (int mb = 0; mb < 2; ++mb) {
+                f4 p;
+                const u2 h2p = pk4_relu(e2[mb]);
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj) {
-                    const float v = __shfl(ypart[mb][jj], 16 * ((lane >> 2) & 3), 64);
-                    if ((lane >> 4) == mb && (lane & 3) == jj) yown = v;
+                    q[mb][jj] = d2[mb][jj] > 0.f ? dy1 * w3a[mb][jj] : 0.f;
+                    p[jj] = e2[mb][jj] > 0.f ? dy2[jj] * w3b[mb] : 0.f;
+                    gb2[mb] += p[jj];
+                    const unsigned hw = h2p[jj >> 1];
+                    gw3[mb] += dy2[jj] * __uint_as_float((jj & 1) ? hw & 0xffff0000u : hw << 16);
                 }
-            const float r = valid ? yown - ts : 0.f;
-            lsum += r * r;
-            L.dy[lane] = 2.f * r * inv_batch;
-        }
-        __syncthreads();
-
-        // ---- backward through layer 3: g_w3, g_b3, dZ2 = dy w3 (Z2 > 0) ----
-        float gw3[2] = {0.f, 0.f}, gb3 = 0.f, gb2[2] = {0.f, 0.f};
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-            for (int jj = 0; jj < 4; ++jj) {
-                const int mrow = 16 * mb + 4 * grp + jj;
-                const float dyr = L.dy[mrow];
-                if (col == 0) gb3 += dyr;
-#pragma unroll
-                for (int nb = 0; nb < 2; ++nb) {
-                    const float zz = z2[mb][nb][jj];
-                    gw3[nb] += dyr * bfr(fmaxf(zz, 0.f));
-                    const float dz = zz > 0.f ? dyr * bfr(m->w3[16 * nb + col]) : 0.f;
-                    gb2[nb] += dz;
-                    L.dZ[mrow * H + 16 * nb + col] = bfu(dz);
-                }
+                dz2p[g][mb] = pk4(p);
             }
-        __syncthreads();
-        // per-lane partials summed over the 4 row groups
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb) {
-            float v = gw3[nb];
-            v += __shfl_xor(v, 16, 64);
-            v += __shfl_xor(v, 32, 64);
-            float u = gb2[nb];
-            u += __shfl_xor(u, 16, 64);
-            u += __shfl_xor(u, 32, 64);
-            if (grp == 0) {
-                sg[wv][MLP_H * MLP_IN + MLP_H + MLP_H * MLP_H + MLP_H + 16 * nb + col] += v;  // w3
-                sg[wv][MLP_H * MLP_IN + MLP_H + MLP_H * MLP_H + 16 * nb + col] += u;          // b2
-            }
+            dz2s[g] = op8(pk4(q[0]), pk4(q[1]));
         }
-        {
-            float v = gb3;
+        // dH1 = dZ2 W2, dZ1 = dH1 (Z1 > 0)
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-            if (lane == 0) sg[wv][MLP_NPARAM - 1] += v;
-        }
-
-        // ---- g_W2 (32 x 32) = dZ2^T (32 x 64) H1 (64 x 32) ----
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+        for (int g = 0; g < 4; ++g)
 #pragma unroll
             for (int nb = 0; nb < 2; ++nb) {
-                f4 c = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int kb = 0; kb < 4; ++kb) {
-                    // A(j, s) = dZ[s][j]; B(s, k) = H1[s][k]
-                    const s4 a = frag(L.dZ, 1, H, 16 * mb, 16 * kb, grp, col);
-                    const s4 b = frag(L.H1, 1, H, 16 * nb, 16 * kb, grp, col);
-                    c = mfma(a, b, c);
-                }
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj)
-                    sg[wv][MLP_H * MLP_IN + MLP_H + (16 * mb + 4 * grp + jj) * H + 16 * nb + col] += c[jj];
-            }
-
-        // ---- dH1 (64 x 32) = dZ2 (64 x 32) W2 (32 x 32); dZ1 = dH1 (Z1 > 0) ----
-        float dz1[4][2][4];
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb) {
-                f4 c = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb) {
-                    const s4 a = frag(L.dZ, H, 1, 16 * mb, 16 * kb, grp, col);
-                    // B(j, k) = W2[j][k]: element (k = n0 + col, j = k0 + 4 grp + jj)
-                    const s4 b = frag(sW2, 1, H, 16 * nb, 16 * kb, grp, col);
-                    c = mfma(a, b, c);
-                }
+                f4 d = mfma32(dz2s[g], a2t[nb], splat(0.f));
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj) {
-                    const int mrow = 16 * mb + 4 * grp + jj, ncol = 16 * nb + col;
-                    dz1[mb][nb][jj] = L.Z1[mrow * H + ncol] > 0.f ? c[jj] : 0.f;
+                    d[jj] = e1[g][nb][jj] > 0.f ? d[jj] : 0.f;
+                    gb1[nb] += d[jj];
                 }
+                dz1p[g][nb] = pk4(d);
             }
-        __syncthreads();
-        float gb1[2] = {0.f, 0.f};
+        // g_W2 = dZ2^T H1, g_W1 = dZ1^T X over two batches of 16 samples each
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) {
-                    const int mrow = 16 * mb + 4 * grp + jj;
-                    gb1[nb] += dz1[mb][nb][jj];
-                    L.dZ[mrow * H + 16 * nb + col] = bfu(dz1[mb][nb][jj]);
-                }
-        __syncthreads();
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb) {
-            float u = gb1[nb];
-            u += __shfl_xor(u, 16, 64);
-            u += __shfl_xor(u, 32, 64);
-            if (grp == 0) sg[wv][MLP_H * MLP_IN + 16 * nb + col] += u;
-        }
-
-        // ---- g_W1 (32 x 16) = dZ1^T (32 x 64) X (64 x 16) ----
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb) {
-            f4 c = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kb = 0; kb < 4; ++kb) {
-                const s4 a = frag(L.dZ, 1, H, 16 * mb, 16 * kb, grp, col);
-                const s4 b = frag(L.X, 1, KI, 0, 16 * kb, grp, col);
-                c = mfma(a, b, c);
-            }
+        for (int P = 0; P < 2; ++P) {
+            u2 x0 = {0u, 0u}, x1 = {0u, 0u};
             if (col < MLP_IN) {
+                x0 = *(const u2 *)&sX[wv][col][32 * P + 4 * grp];
+                x1 = *(const u2 *)&sX[wv][col][32 * P + 16 + 4 * grp];
+            }
+            const b8 xo = op8(x0, x1);
 #pragma unroll
-                for (int jj = 0; jj < 4; ++jj) sg[wv][(16 * mb + 4 * grp + jj) * MLP_IN + col] += c[jj];
+            for (int mb = 0; mb < 2; ++mb) {
+                const b8 za = op8(dz2p[2 * P][mb], dz2p[2 * P + 1][mb]);
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb)
+                    gW2[mb][nb] = mfma32(za, op8(h1p[2 * P][nb], h1p[2 * P + 1][nb]), gW2[mb][nb]);
+                gW1[mb] = mfma32(op8(dz1p[2 * P][mb], dz1p[2 * P + 1][mb]), xo, gW1[mb]);
             }
         }
-        __syncthreads();
+    }
+
+    // the wave's sums in parameter order
+    float *o = sg[wv];
+    constexpr int B1 = H * MLP_IN, W2 = B1 + H, B2 = W2 + H * H, W3 = B2 + H;
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb) {
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+            const int unit = 16 * mb + 4 * grp + jj;
+            if (col < MLP_IN) o[unit * MLP_IN + col] = gW1[mb][jj];
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb) o[W2 + unit * H + 16 * nb + col] = gW2[mb][nb][jj];
+        }
+        float u = gb1[mb], v = gb2[mb], w = gw3[mb];
+        u += __shfl_xor(u, 16, 64);
+        v += __shfl_xor(v, 16, 64);
+        w += __shfl_xor(w, 16, 64);
+        u += __shfl_xor(u, 32, 64);
+        v += __shfl_xor(v, 32, 64);
+        w += __shfl_xor(w, 32, 64);
+        if (grp == 0) {
+            o[B1 + 16 * mb + col] = u;
+            o[B2 + 16 * mb + col] = v;
+            o[W3 + 16 * mb + col] = w;
+        }
+    }
+    gb3 += __shfl_xor(gb3, 16, 64);
+    gb3 += __shfl_xor(gb3, 32, 64);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off, 64);
+    if (lane == 0) {
+        o[MLP_NPARAM - 1] = gb3;
+        o[MLP_NPARAM] = lsum;
     }
     __syncthreads();
     // workgroup partial (fixed wave order)
-    for (int i = threadIdx.x; i < MLP_NPARAM; i += 64 * TW) {
+    for (int i = threadIdx.x; i <= MLP_NPARAM; i += 64 * TW) {
         float v = 0.f;
 #pragma unroll
         for (int w = 0; w < TW; ++w) v += sg[w][i];
-        partial[(int64_t)blockIdx.x * MLP_NPARAM + i] = v;
-    }
-    // loss partial
-    {
-        float v = lsum;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-        __shared__ float sl[TW];
-        if (lane == 0) sl[wv] = v;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            float a = 0.f;
-            for (int w = 0; w < TW; ++w) a += sl[w];
-            loss_partial[blockIdx.x] = a * inv_batch;
-        }
+        if (i < MLP_NPARAM) partial[(int64_t)blockIdx.x * MLP_NPARAM + i] = v;
+        else loss_partial[blockIdx.x] = v * inv_batch;
     }
 }
 
 // Fixed-order sum of the workgroup partials.  Workgroup g takes parameters
-// 64 g .. 64 g + 63 (the workgroup after the last one the loss); its wave w
-// sums rows w R .. w R + R - 1 in order (R = nblocks / GR_W rounded up), one
-// parameter per lane, and the GR_W wave sums are then added in wave order
-// through LDS: the same order on every call, and every wave's loads are
-// independent of each other (one pass per row instead of one per parameter
-// and row).  With ad.m set, the lane that formed a parameter's gradient also
-// takes that parameter's Adam step (elementwise, so no other workgroup waits).
-constexpr int GR_W = 16;  // waves per workgroup of the gradient sum
+// 16 g .. 16 g + 15 (the loss counts as one more), 64 rows at a time: thread
+// (slot = thread / 16, column = thread % 16) adds rows slot, slot + 64, ...,
+// and the 64 slots are added as a tree within each wavefront and in wave order
+// after it: the same order on every call.  One launch's latency bounds it, so
+// at the most rows (256) each thread has its four loads under way at once and
+// 79 workgroups share them (20 workgroups of 64 columns, 16 loads a thread,
+// took 6.7 us).  With ad.m set, the thread that formed a parameter's gradient
+// also takes that parameter's Adam step (elementwise, so no other workgroup
+// waits), on values it has loaded meanwhile.
+constexpr int GR_C = 16, GR_S = 64;
+static_assert(TRAIN_BLOCKS <= 4 * GR_S, "k_grad_reduce takes 4 rows per thread");
 
-__global__ void __launch_bounds__(64 * GR_W) k_grad_reduce(const float *__restrict__ partial, int nblocks,
-                                                           const float *__restrict__ loss_partial,
-                                                           float *__restrict__ grad, float *__restrict__ loss,
-                                                           AdamStep ad)
+__global__ void __launch_bounds__(GR_C *GR_S) k_grad_reduce(const float *__restrict__ partial, int nblocks,
+                                                            const float *__restrict__ loss_partial,
+                                                            float *__restrict__ grad, float *__restrict__ loss,
+                                                            AdamStep ad)
 {
-    __shared__ float sp[GR_W][64];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const bool is_loss = (int)blockIdx.x == (MLP_NPARAM + 63) / 64;
-    const int i = (int)blockIdx.x * 64 + lane;
-    const int rows = (nblocks + GR_W - 1) / GR_W;
-    const int b0 = w * rows, b1 = min(b0 + rows, nblocks);
-    float s = 0.f;
-    if (is_loss) {
-        if (lane == 0)
-            for (int b = b0; b < b1; ++b) s += loss_partial[b];
-    } else if (i < MLP_NPARAM) {
-        for (int b = b0; b < b1; ++b) s += partial[(int64_t)b * MLP_NPARAM + i];
-    }
-    sp[w][lane] = s;
-    __syncthreads();
-    if (w == 0) {
-        float g = 0.f;
+    __shared__ float sp[GR_S / 4][GR_C];
+    const int col = threadIdx.x & 15, slot = threadIdx.x >> 4;
+    const int i = (int)blockIdx.x * GR_C + col;
+    const bool is_loss = i == MLP_NPARAM, on = i <= MLP_NPARAM;
+    const float *src = is_loss ? loss_partial : partial + i;
+    const int64_t st = is_loss ? 1 : MLP_NPARAM;
+    float r[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int k = 0; k < GR_W; ++k) g += sp[k][lane];
-        if (is_loss) {
-            if (lane == 0) *loss = g;
-        } else if (i < MLP_NPARAM) {
-            grad[i] = g;
-            if (ad.m) {
-                float *p = reinterpret_cast<float *>(ad.m) + i;  // MlpDevice is the flat parameter vector (ABI order)
-                const float a = ad.b1 * ad.m1[i] + ad.ob1 * g;
-                const float v = ad.b2 * ad.m2[i] + ad.ob2 * g * g;
-                ad.m1[i] = a;
-                ad.m2[i] = v;
-                *p -= ad.lr * (a * ad.c1) / (sqrtf(v * ad.c2) + ad.eps);
-            }
-        }
+    for (int k = 0; k < 4; ++k)
+        if (on && slot + GR_S * k < nblocks) r[k] = src[(slot + GR_S * k) * st];
+    const bool adam = ad.m && threadIdx.x < GR_C && i < MLP_NPARAM;
+    float *p = reinterpret_cast<float *>(ad.m) + i;  // MlpDevice is the flat parameter vector (ABI order)
+    float a0 = 0.f, v0 = 0.f, p0 = 0.f;
+    if (adam) {
+        a0 = ad.m1[i];
+        v0 = ad.m2[i];
+        p0 = *p;
+    }
+    float s = (r[0] + r[1]) + (r[2] + r[3]);
+    s += __shfl_xor(s, 16, 64);
+    s += __shfl_xor(s, 32, 64);
+    if ((slot & 3) == 0) sp[slot >> 2][col] = s;
+    __syncthreads();
+    if (threadIdx.x >= GR_C || !on) return;
+    float g = 0.f;
+#pragma unroll
+    for (int k = 0; k < GR_S / 4; ++k) g += sp[k][col];
+    if (is_loss) {
+        *loss = g;
+        return;
+    }
+    grad[i] = g;
+    if (adam) {
+        const float a = ad.b1 * a0 + ad.ob1 * g;
+        const float v = ad.b2 * v0 + ad.ob2 * g * g;
+        ad.m1[i] = a;
+        ad.m2[i] = v;
+        *p = p0 - ad.lr * (a * ad.c1) / (sqrtf(v * ad.c2) + ad.eps);
     }
 }
 
@@ -512,9 +469,12 @@ hipError_t launch_train_grad(const MlpDevice *m, const float *x, const float *t,
                              float *partial, float *loss_partial, int nblocks, float *grad, float *loss,
                              const AdamStep &adam, hipStream_t s)
 {
+    // one tile per wavefront as far as the partial rows (TRAIN_BLOCKS) go
+    const int64_t want = (batch + TS * TW - 1) / (TS * TW);
+    if (want < nblocks) nblocks = (int)want;
     hipLaunchKernelGGL(k_train_grad, dim3(nblocks), dim3(64 * TW), 0, s, m, x, t, idx, batch, 1.0f / (float)batch,
                        partial, loss_partial);
-    hipLaunchKernelGGL(k_grad_reduce, dim3((MLP_NPARAM + 63) / 64 + 1), dim3(64 * GR_W), 0, s, partial, nblocks,
+    hipLaunchKernelGGL(k_grad_reduce, dim3(MLP_NPARAM / GR_C + 1), dim3(GR_C * GR_S), 0, s, partial, nblocks,
                        loss_partial, grad, loss, adam);
     return hipGetLastError();
 }
