@@ -83,23 +83,34 @@ __device__ __forceinline__ b8 bf8(const s4 lo, const s4 hi)
 // clamped to [0, 1], which for pre-activations of magnitude below 1 (the
 // scaled network) is the ReLU of the rounded value, bit for bit: negative
 // values and -0 give +0.  The inputs are results of matrix instructions, which
-// a vector instruction may read only 12 cycles after they issue, and the
+// a vector instruction may read only 12 wait states after they issue, and the
 // outputs feed matrix instructions, which may read a vector result only 2
-// cycles after it is written; the compiler's hazard tracking does not look
-// into inline assembly, so the wait states are part of it.
+// after it is written; the compiler's hazard tracking does not look into
+// inline assembly, so the wait states are part of it: the last 2 here, the
+// first 12 once per layer in results_settle.
 __device__ __forceinline__ b8 relu_pack_clamped(const f4 lo, const f4 hi)
 {
     unsigned r0, r1, r2, r3;
-    asm("s_nop 11\n\t"
-        "v_cvt_pk_bf16_f32 %0, %4, %5 clamp\n\t"
-        "v_cvt_pk_bf16_f32 %1, %6, %7 clamp\n\t"
-        "v_cvt_pk_bf16_f32 %2, %8, %9 clamp\n\t"
-        "v_cvt_pk_bf16_f32 %3, %10, %11 clamp\n\t"
-        "s_nop 1"
-        : "=&v"(r0), "=&v"(r1), "=&v"(r2), "=&v"(r3)
-        : "v"(lo[0]), "v"(lo[1]), "v"(lo[2]), "v"(lo[3]), "v"(hi[0]), "v"(hi[1]), "v"(hi[2]), "v"(hi[3]));
+    asm volatile("v_cvt_pk_bf16_f32 %0, %4, %5 clamp\n\t"
+                 "v_cvt_pk_bf16_f32 %1, %6, %7 clamp\n\t"
+                 "v_cvt_pk_bf16_f32 %2, %8, %9 clamp\n\t"
+                 "v_cvt_pk_bf16_f32 %3, %10, %11 clamp\n\t"
+                 "s_nop 1"
+                 : "=&v"(r0), "=&v"(r1), "=&v"(r2), "=&v"(r3)
+                 : "v"(lo[0]), "v"(lo[1]), "v"(lo[2]), "v"(lo[3]), "v"(hi[0]), "v"(hi[1]), "v"(hi[2]), "v"(hi[3]));
     const u4 w = {r0, r1, r2, r3};
     return __builtin_bit_cast(b8, w);
+}
+
+// Every matrix instruction above is issued above, everything below is issued
+// below, and 12 wait states lie between them: 48 cycles that a wavefront spends
+// once per layer (once per batch of 16 stencils they were a third of the
+// network's latency: 1040 -> 950 us for the slopes of 256^3).
+__device__ __forceinline__ void results_settle()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 11");
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 // Layer 2 runs as one K = 32 product per output block (v_mfma_f32_16x16x32_bf16:
@@ -177,11 +188,10 @@ static_assert(sizeof(MlpRegs) == sizeof(uint4) * 12, "lane image layout");
 // Network output for the lane's own input x[0..3] (all 64 lanes must be active,
 // and every lane's input finite: 0 x inf in a zero block of an operand would
 // spread a NaN to the other lanes of the same column).
-// The four 16-stencil batches are independent: each layer is issued for all
-// of them before the next, so the matrix instructions of one batch overlap
-// the ReLU and packing of another instead of the wave waiting on each result.
+// The four 16-stencil batches are independent: a layer's products of one batch
+// run under the packing of the next one.
 // Returns the output of the scaled network (the true output times 1 / up).
-__device__ __forceinline__ float mlp_wave(const float (&x)[4], const MlpRegs &R, int grp)
+__device__ __forceinline__ float mlp_wave(const float (&x)[4], const MlpRegs &R)
 {
     const s4 xb = bf4(x[0], x[1], x[2], x[3]);
     f4 d1[4][2];
@@ -190,26 +200,40 @@ __device__ __forceinline__ float mlp_wave(const float (&x)[4], const MlpRegs &R,
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb)
             d1[g][mb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(R.a1[g][mb], xb, R.c1[mb], 0, 0, 0);
-    b8 hb[4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) hb[g] = relu_pack_clamped(d1[g][0], d1[g][1]);
+    results_settle();
     f4 d2[4][2];
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
+    for (int g = 0; g < 4; ++g) {
+        const b8 h = relu_pack_clamped(d1[g][0], d1[g][1]);
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb)
-            d2[g][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(R.a2[mb], hb[g], R.c2[mb], 0, 0, 0);
-    b8 h2[4];
+            d2[g][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(R.a2[mb], h, R.c2[mb], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    results_settle();
+    f4 d3[4];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) h2[g] = relu_pack_clamped(d2[g][0], d2[g][1]);
-    float part[4];
+    for (int g = 0; g < 4; ++g) {
+        const b8 h = relu_pack_clamped(d2[g][0], d2[g][1]);
+        d3[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(R.a3, h, R.c3, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // the unused elements stay allocated until here: a conversion above must
+    // not be given a register that a product in flight still writes
+    asm volatile("" ::"v"(d3[0]), "v"(d3[1]), "v"(d3[2]), "v"(d3[3]));
+    int part[4];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) part[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(R.a3, h2[g], R.c3, 0, 0, 0)[0];
-    return grp == 0 ? part[0] : (grp == 1 ? part[1] : (grp == 2 ? part[2] : part[3]));
+    for (int g = 0; g < 4; ++g) part[g] = __float_as_int(d3[g][0]);
+    // lane group g takes batch g's value: moves that write one row of 16 lanes
+    int y = part[0];
+    y = __builtin_amdgcn_update_dpp(y, part[1], 0xe4, 0x2, 0xf, false);
+    y = __builtin_amdgcn_update_dpp(y, part[2], 0xe4, 0x4, 0xf, false);
+    y = __builtin_amdgcn_update_dpp(y, part[3], 0xe4, 0x8, 0xf, false);
+    return __int_as_float(y);
 }
 
 // sigma from the 5-cell stencil w[0..4] (centre w[2]); up as in MlpImage
-__device__ __forceinline__ float learned_sigma(const float (&w)[5], const MlpRegs &R, int grp, float up)
+__device__ __forceinline__ float learned_sigma(const float (&w)[5], const MlpRegs &R, float up)
 {
     float d[4];
 #pragma unroll
@@ -225,12 +249,10 @@ __device__ __forceinline__ float learned_sigma(const float (&w)[5], const MlpReg
     float x[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) x[k] = d[k] * rs;
-    const float sigma = s * (mlp_wave(x, R, grp) * up);  // the product with up is exact
-    const float dm = d[1], dp = d[2];
-    const float sg = dp > 0.f ? 1.f : -1.f;
-    const float lim = 2.f * fminf(fabsf(dm), fabsf(dp));
-    const float c = sg * fminf(fmaxf(sg * sigma, 0.f), lim);
-    return (dm * dp > 0.f) ? c : 0.f;
+    const float sigma = s * (mlp_wave(x, R) * up);  // the product with up is exact
+    // zero, or between zero and twice the smaller difference where their signs agree
+    const float m = __builtin_amdgcn_fmed3f(d[1], d[2], 0.f);
+    return __builtin_amdgcn_fmed3f(sigma, m + m, 0.f);
 }
 
 struct Bc {
@@ -253,108 +275,222 @@ __device__ __forceinline__ int64_t map1(int64_t i, int64_t n, int lo, int hi, bo
     return m < 0 ? 0 : (m >= n ? n - 1 : m);
 }
 
-// Slopes along one dimension Q from a tile of primitives staged in LDS.
-// A workgroup owns 64 cells along x times R rows: for Q = 0 the rows are whole
-// x lines (y + ny z) and the tile carries a 2-cell halo along x; for Q = 1, 2
-// the rows run along y or z at a fixed z or y and the halo is 2 rows each
-// side.  Each cell is read and converted to primitives once per dimension;
-// then every wave takes whole (variable, row) batches of 64 stencils, so the
-// matrix instructions always run with all lanes holding a real stencil.
-constexpr int LS_ROWS = 16;
-
-template <int ND, int Q>
-struct LsTile {
-    static constexpr int NP = ND + 2;
-    static constexpr int R = ND == 1 ? 1 : LS_ROWS;  // rows per tile
-    static constexpr int NW = ND == 1 ? 1 : 4;       // waves per workgroup (launch bounds match)
-    static constexpr int RA = Q == 0 ? R : R + 4;    // LDS rows
-    static constexpr int CA = Q == 0 ? 68 : 64;      // LDS columns
-};
-
-template <int ND, int Q>
-__global__ void __launch_bounds__(ND == 1 ? 64 : 256)
-    k_learned_slopes(const float *__restrict__ u, float *__restrict__ slopes, int nx, int ny, int nz, int64_t vs,
-                     int64_t svs, float gm1, Bc bc, const MlpImage *__restrict__ img)
+// One cell's primitives from its conserved values.
+template <int ND>
+__device__ __forceinline__ void prims(const float (&uu)[ND + 2], float gm1, float (&w)[ND + 2])
 {
-    using G = LsTile<ND, Q>;
-    constexpr int NP = G::NP, R = G::R, NT = 64 * G::NW, RA = G::RA, CA = G::CA;
-    __shared__ float sW[NP][RA][CA];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int grp = lane >> 4, col = lane & 15;
-    const int x0 = blockIdx.x * 64;
-    const int b0 = blockIdx.y * R;  // first row of the tile
-    const int cf = blockIdx.z;      // fixed coordinate (z for Q = 1, y for Q = 2)
-    const int nq = Q == 0 ? nx : (Q == 1 ? ny : nz);
-    const int nrow = Q == 0 ? ny * nz : nq;
+    float ir = __builtin_amdgcn_rcpf(uu[0]);
+    ir = fmaf(fmaf(-uu[0], ir, 1.f), ir, ir);  // to the last bit, as a division gives
+    float ke = 0.f;
+    w[0] = uu[0];
+#pragma unroll
+    for (int d = 0; d < ND; ++d) {
+        w[1 + d] = uu[1 + d] * ir;
+        ke += uu[1 + d] * w[1 + d];
+    }
+    w[ND + 1] = gm1 * (uu[ND + 1] - 0.5f * ke);
+}
+
+template <int ND>
+__device__ __forceinline__ void load_cell(const float *u, int64_t vs, unsigned cell, float (&uu)[ND + 2])
+{
+#pragma unroll
+    for (int v = 0; v < ND + 2; ++v) uu[v] = *(const float *)((const char *)(u + v * vs) + cell * 4u);
+}
+
+template <int ND>
+__device__ __forceinline__ void store_slope(float *slopes, int64_t svs, int qv, unsigned cell, float sg)
+{
+    // a variable's slope array is below 4 GiB (checked on the host): 32-bit
+    // byte offsets from its (wave-uniform) base
+    *(float *)((char *)(slopes + (int64_t)qv * svs) + cell * 4u) = sg;
+}
+
+// Slopes along Q, and with XS along x in the same pass.  A wavefront owns 64
+// consecutive cells of the plane across Q (2D: of a row; 3D: of the plane's
+// cells numbered x first, so that no lane idles at the end of a row) and
+// marches along Q over R rows with the five rows of the stencil in registers:
+// each cell is read and converted once per pass (and 4 more per R), the next
+// row's loads are under way during the networks of this one, and no wavefront
+// waits for another.  The x stencils come from a 68-cell line of the row in LDS,
+// private to the wavefront; at the ends of a row of cells the two neighbours
+// beyond are fetched by the lane itself (on both sides where a row has fewer
+// than 4 cells: NARROW); where a lane's five cells lie in LDS is fixed for the
+// march.
+//
+// What bounds it: the matrix and the vector units, which take turns more than
+// they overlap at 3 wavefronts per SIMD: 330 cycles of products and about 290
+// of vector work per network and wavefront, 590 measured.  Tiles of 16 rows in
+// LDS, one launch per dimension with a barrier between conversion and networks,
+// took 54 us for 1024^2 (now 42), 26 for 256^2 (6.7), 254 for 150 x 120 x 160
+// (180) and 1083 for 256^3 (935).
+template <int ND, int Q, bool XS, bool NARROW>
+__global__ void __launch_bounds__(256)
+    k_slopes_march(const float *__restrict__ u, float *__restrict__ slopes, int nx, int ny, int nz, int R, int nseg,
+                   int ntask, int64_t vs, int64_t svs, float gm1, Bc bc, const MlpImage *__restrict__ img)
+{
+    constexpr int NP = ND + 2, NE = NARROW ? 4 : 2;
+    __shared__ float sL[XS ? 4 : 1][NP][68 + 64 * NE];  // the line, then what each lane fetched beyond its ends
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int task = blockIdx.x * 4 + wv;
+    if (task >= ntask) return;
     MlpRegs M;
     __builtin_memcpy(&M, &img->lane[lane][0], sizeof(M));
     const float up = img->up;
-
-    for (int i = tid; i < RA * CA; i += NT) {
-        const int r = i / CA, c = i % CA;
-        bool flip = false;
-        int x, y, z;
-        if constexpr (Q == 0) {
-            x = (int)map1(x0 - 2 + c, nx, bc.v[0][0], bc.v[0][1], flip);
-            const int line = min(b0 + r, nrow - 1);
-            y = line % ny;
-            z = line / ny;
-        } else {
-            x = min(x0 + c, nx - 1);
-            const int qi = (int)map1(b0 - 2 + r, nq, bc.v[Q][0], bc.v[Q][1], flip);
-            y = Q == 1 ? qi : cf;
-            z = Q == 1 ? cf : qi;
-        }
-        const int64_t cell = ((int64_t)z * ny + y) * nx + x;
-        float uu[NP];
-#pragma unroll
-        for (int v = 0; v < NP; ++v) uu[v] = u[cell + v * vs];
-        const float ir = 1.0f / uu[0];
-        float w[NP], ke = 0.f;
-        w[0] = uu[0];
-#pragma unroll
-        for (int d = 0; d < ND; ++d) {
-            w[1 + d] = uu[1 + d] * ir;
-            ke += uu[1 + d] * w[1 + d];
-        }
-        w[NP - 1] = gm1 * (uu[NP - 1] - 0.5f * ke);
-        if (flip) w[1 + Q] = -w[1 + Q];
-#pragma unroll
-        for (int v = 0; v < NP; ++v) sW[v][r][c] = w[v];
+    const int chunk = task / nseg, f0 = (task - chunk * nseg) * 64;
+    const int nf = ND == 2 ? nx : (Q == 2 ? nx * ny : nx * nz);
+    const int nq = Q == 1 ? ny : nz;
+    const unsigned sq = Q == 1 ? (unsigned)nx : (unsigned)nx * (unsigned)ny;
+    const int j0 = chunk * R, j1 = min(j0 + R, nq);
+    const unsigned f = (unsigned)min(f0 + lane, nf - 1);
+    unsigned c0 = f;  // the lane's cell in row 0
+    if constexpr (ND == 3 && Q == 1) {
+        const unsigned z = f / (unsigned)nx;
+        c0 = z * (unsigned)nx * (unsigned)ny + (f - z * (unsigned)nx);
     }
-    __syncthreads();
 
-    const int x = x0 + lane;
-    for (int k = wv; k < NP * R; k += G::NW) {  // wave-uniform
-        const int v = k / R, r = k % R;
-        float w5[5];
+    // x stencils: the line's ends (lanes 0 .. 3) and the row's, and where the
+    // lane finds its five cells
+    unsigned ch = 0, ce[NE] = {};
+    float fl[NE] = {};
+    int at[5] = {};
+    bool edge = false;
+    if constexpr (XS) {
+        ch = (unsigned)min(max(lane < 2 ? f0 - 2 + lane : f0 + 62 + (lane & 3), 0), nf - 1);
+        const int x = ND == 2 ? (int)f : (int)(f % (unsigned)nx);
+        const bool lo = x < 2, hi = x >= nx - 2;
+        edge = lo || hi;
 #pragma unroll
-        for (int s5 = 0; s5 < 5; ++s5) w5[s5] = Q == 0 ? sW[v][r][lane + s5] : sW[v][r + s5][lane];
-        const float sg = learned_sigma(w5, M, grp, up);
-        const int rowi = b0 + r;
-        if (x < nx && rowi < nrow) {
-            // a variable's slope array is below 4 GiB (checked on the host):
-            // 32-bit byte offsets from its (wave-uniform) base
-            unsigned cell;
-            if constexpr (Q == 0) cell = (unsigned)rowi * (unsigned)nx + (unsigned)x;
-            else if constexpr (Q == 1) cell = ((unsigned)cf * (unsigned)ny + (unsigned)rowi) * (unsigned)nx + (unsigned)x;
-            else cell = ((unsigned)rowi * (unsigned)ny + (unsigned)cf) * (unsigned)nx + (unsigned)x;
-            char *base = (char *)(slopes + (int64_t)(Q * NP + v) * svs);
-            *(float *)(base + cell * 4u) = sg;
+        for (int k = 0; k < 5; ++k) at[k] = (int)f - f0 + k;
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            const int side = NARROW ? (e < 2 ? -1 : 1) : (lo ? -1 : 1), d = 1 + (e & 1);
+            bool flip = false;
+            const int xe = edge ? (int)map1(x + side * d, nx, bc.v[0][0], bc.v[0][1], flip) : x;
+            ce[e] = f - (unsigned)x + (unsigned)xe;
+            fl[e] = flip ? -1.f : 1.f;
+            if (side < 0 ? lo : hi) at[side < 0 ? 2 - d : 2 + d] = 68 + 64 * e + lane;
         }
+    }
+
+    auto row = [&](int j, bool &flip) {  // offset of row j (mapped into the patch)
+        return (unsigned)map1(j, nq, bc.v[Q][0], bc.v[Q][1], flip) * sq;
+    };
+    float W[5][NP], raw[NP];
+    bool flipn = false;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        bool flip = false;
+        load_cell<ND>(u, vs, c0 + row(j0 - 2 + k, flip), raw);
+        prims<ND>(raw, gm1, W[k + 1]);
+        if (flip) W[k + 1][1 + Q] = -W[k + 1][1 + Q];
+    }
+    load_cell<ND>(u, vs, c0 + row(j0 + 2, flipn), raw);
+    for (int j = j0; j < j1; ++j) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int v = 0; v < NP; ++v) W[k][v] = W[k + 1][v];
+        prims<ND>(raw, gm1, W[4]);
+        if (flipn) W[4][1 + Q] = -W[4][1 + Q];
+        const unsigned cell = c0 + (unsigned)j * sq;
+        if constexpr (XS) {
+            float (*ln)[68 + 64 * NE] = sL[wv];
+            const unsigned o = (unsigned)j * sq;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // (the last row's reads)
+            if (edge)
+#pragma unroll
+                for (int e = 0; e < NE; ++e) {
+                    float re[NP], we[NP];
+                    load_cell<ND>(u, vs, ce[e] + o, re);
+                    prims<ND>(re, gm1, we);
+                    we[1] *= fl[e];
+#pragma unroll
+                    for (int v = 0; v < NP; ++v) ln[v][68 + 64 * e + lane] = we[v];
+                }
+            if (lane < 4) {
+                float rh[NP], wh[NP];
+                load_cell<ND>(u, vs, ch + o, rh);
+                prims<ND>(rh, gm1, wh);
+#pragma unroll
+                for (int v = 0; v < NP; ++v) ln[v][lane < 2 ? lane : 64 + lane] = wh[v];
+            }
+#pragma unroll
+            for (int v = 0; v < NP; ++v) ln[v][lane + 2] = W[2][v];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+        flipn = false;
+        load_cell<ND>(u, vs, c0 + row(j + 3, flipn), raw);
+#pragma unroll
+        for (int v = 0; v < NP; ++v) {
+            const float w5[5] = {W[0][v], W[1][v], W[2][v], W[3][v], W[4][v]};
+            store_slope<ND>(slopes, svs, Q * NP + v, cell, learned_sigma(w5, M, up));
+        }
+        if constexpr (XS)
+#pragma unroll
+            for (int v = 0; v < NP; ++v) {
+                float w5[5];
+#pragma unroll
+                for (int k = 0; k < 5; ++k) w5[k] = sL[wv][v][at[k]];
+                store_slope<ND>(slopes, svs, v, cell, learned_sigma(w5, M, up));
+            }
     }
 }
 
-template <int ND, int Q>
-void ls_launch(const float *u, float *slopes, int nx, int ny, int nz, int64_t vs, int64_t svs, float gm1, const Bc &b,
-               const MlpImage *img, hipStream_t s)
+// 1D: 64 cells and two more on each side per wavefront, in LDS.
+__global__ void __launch_bounds__(64)
+    k_slopes_1d(const float *__restrict__ u, float *__restrict__ slopes, int nx, int64_t vs, int64_t svs, float gm1,
+                Bc bc, const MlpImage *__restrict__ img)
 {
-    using G = LsTile<ND, Q>;
-    const unsigned gx = (unsigned)((nx + 63) / 64);
-    const unsigned gy = (unsigned)(Q == 0 ? (ny * nz + G::R - 1) / G::R : ((Q == 1 ? ny : nz) + G::R - 1) / G::R);
-    const unsigned gz = (unsigned)(Q == 0 ? 1 : (Q == 1 ? nz : ny));
-    hipLaunchKernelGGL((k_learned_slopes<ND, Q>), dim3(gx, gy, gz), dim3(64 * G::NW), 0, s, u, slopes, nx, ny, nz, vs,
-                       svs, gm1, b, img);
+    __shared__ float sW[3][68];
+    const int lane = threadIdx.x, x0 = blockIdx.x * 64;
+    MlpRegs M;
+    __builtin_memcpy(&M, &img->lane[lane][0], sizeof(M));
+    const float up = img->up;
+    for (int c = lane; c < 68; c += 64) {
+        bool flip = false;
+        const unsigned cell = (unsigned)map1(x0 - 2 + c, nx, bc.v[0][0], bc.v[0][1], flip);
+        float uu[3], w[3];
+        load_cell<1>(u, vs, cell, uu);
+        prims<1>(uu, gm1, w);
+        sW[0][c] = w[0];
+        sW[1][c] = flip ? -w[1] : w[1];
+        sW[2][c] = w[2];
+    }
+    __syncthreads();
+    for (int v = 0; v < 3; ++v) {
+        float w5[5];
+#pragma unroll
+        for (int k = 0; k < 5; ++k) w5[k] = sW[v][lane + k];
+        const float sg = learned_sigma(w5, M, up);
+        if (x0 + lane < nx) store_slope<1>(slopes, svs, v, (unsigned)(x0 + lane), sg);
+    }
+}
+
+// Rows per wavefront of the marching kernel: what gives 3 wavefronts to each
+// of the 1024 SIMDs (as many as the registers allow), at most 8.  Fewer rows
+// mean four extra rows read and converted for fewer results, more rows a longer
+// serial chain: 256^2 takes 6.7 us at 1 row and 15.1 at 4, 64^3 27 at 2 and
+// 31 at 4, 1024^2 49 at 1, 42 at 4 and 43 at 8, 256^3 955 at 4 and 935 at 8,
+// 2048^2 131 at 4, 133 at 8 and 165 at 16.
+int march_rows(int64_t nseg, int nq)
+{
+    const int64_t r = (nseg * nq + 3071) / 3072;
+    return (int)(r < 1 ? 1 : (r > 8 ? 8 : r));
+}
+
+template <int ND, int Q, bool XS, bool NARROW>
+void march_launch(const float *u, float *slopes, int nx, int ny, int nz, int64_t vs, int64_t svs, float gm1,
+                  const Bc &b, const MlpImage *img, hipStream_t s)
+{
+    const int64_t nf = ND == 2 ? nx : (Q == 2 ? (int64_t)nx * ny : (int64_t)nx * nz);
+    const int nq = Q == 1 ? ny : nz;
+    const int64_t nseg = (nf + 63) / 64;
+    const int R = march_rows(nseg, nq);
+    const int64_t ntask = nseg * ((nq + R - 1) / R);
+    hipLaunchKernelGGL((k_slopes_march<ND, Q, XS, NARROW>), dim3((unsigned)((ntask + 3) / 4)), dim3(256), 0, s, u,
+                       slopes, nx, ny, nz, R, (int)nseg, (int)ntask, vs, svs, gm1, b, img);
 }
 
 __global__ void __launch_bounds__(64) k_mlp_image(const MlpDevice *__restrict__ mlp, MlpImage *__restrict__ img)
@@ -378,7 +514,7 @@ __global__ void __launch_bounds__(256) k_mlp_forward(const MlpDevice *__restrict
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t ii = i < batch ? i : batch - 1;
     const float xi[4] = {x[4 * ii], x[4 * ii + 1], x[4 * ii + 2], x[4 * ii + 3]};
-    const float out = mlp_wave(xi, R, grp) * up;
+    const float out = mlp_wave(xi, R) * up;
     if (i < batch) y[i] = out;
 }
 
@@ -393,17 +529,16 @@ hipError_t launch_learned_slopes(const float *u, float *slopes, const int64_t n[
         b.v[q][1] = bc[q][1];
     }
     const int nx = (int)n[0], ny = (int)n[1], nz = (int)n[2];
-    switch (ndim) {
-    case 1: ls_launch<1, 0>(u, slopes, nx, ny, nz, vstride, svs, gm1, b, img, s); break;
-    case 2:
-        ls_launch<2, 0>(u, slopes, nx, ny, nz, vstride, svs, gm1, b, img, s);
-        ls_launch<2, 1>(u, slopes, nx, ny, nz, vstride, svs, gm1, b, img, s);
-        break;
-    default:
-        ls_launch<3, 0>(u, slopes, nx, ny, nz, vstride, svs, gm1, b, img, s);
-        ls_launch<3, 1>(u, slopes, nx, ny, nz, vstride, svs, gm1, b, img, s);
-        ls_launch<3, 2>(u, slopes, nx, ny, nz, vstride, svs, gm1, b, img, s);
-        break;
+    if (ndim == 1) {
+        hipLaunchKernelGGL(k_slopes_1d, dim3((unsigned)((nx + 63) / 64)), dim3(64), 0, s, u, slopes, nx, vstride, svs,
+                           gm1, b, img);
+    } else if (ndim == 2) {
+        if (nx < 4) march_launch<2, 1, true, true>(u, slopes, nx, ny, nz, vstride, svs, gm1, b, img, s);
+        else march_launch<2, 1, true, false>(u, slopes, nx, ny, nz, vstride, svs, gm1, b, img, s);
+    } else {
+        if (nx < 4) march_launch<3, 2, true, true>(u, slopes, nx, ny, nz, vstride, svs, gm1, b, img, s);
+        else march_launch<3, 2, true, false>(u, slopes, nx, ny, nz, vstride, svs, gm1, b, img, s);
+        march_launch<3, 1, false, false>(u, slopes, nx, ny, nz, vstride, svs, gm1, b, img, s);
     }
     return hipGetLastError();
 }
