@@ -68,6 +68,11 @@ __device__ __forceinline__ void reflux_faces(T *u, const Grid &g, const Box &b, 
     const int ffaces = faces * A1 * A2, fn1 = b.n[R1] * A1;
     if (t >= faces) return;
     const int t1 = t % b.n[R1], t2 = t / b.n[R1];
+    // all of both sides' loads first: the stores could alias them as far as
+    // the compiler knows, and each variable would wait for the one before
+    T x[2][ND + 2];
+    double corr[2][ND + 2];
+    int64_t c[2];
 #pragma unroll
     for (int side = 0; side < 2; ++side) {
         const double *cf = side == 0 ? c_lo : c_hi;
@@ -76,7 +81,7 @@ __device__ __forceinline__ void reflux_faces(T *u, const Grid &g, const Box &b, 
         c3[Q] = side == 0 ? b.lo[Q] - 1 : b.lo[Q] + b.n[Q];
         c3[R1] = b.lo[R1] + t1;
         c3[R2] = b.lo[R2] + t2;
-        const int64_t c = at(g, c3[0], c3[1], c3[2]);
+        c[side] = at(g, c3[0], c3[1], c3[2]);
 #pragma unroll
         for (int v = 0; v < ND + 2; ++v) {
             double sum = 0.0;
@@ -87,11 +92,14 @@ __device__ __forceinline__ void reflux_faces(T *u, const Grid &g, const Box &b, 
                     sum += ff[(int64_t)v * ffaces + (A2 * t2 + o2) * fn1 + A1 * t1 + o1];
             const double phi_f = sum / (double)(A1 * A2);
             const double phi_c = cf[(int64_t)v * faces + t];
-            const double corr = side == 0 ? phi_c - phi_f : phi_f - phi_c;
-            T &x = u[v * g.vs + c];
-            x = (T)fma_(corr, idq, (double)x);
+            corr[side][v] = side == 0 ? phi_c - phi_f : phi_f - phi_c;
+            x[side][v] = u[v * g.vs + c[side]];
         }
     }
+#pragma unroll
+    for (int side = 0; side < 2; ++side)
+#pragma unroll
+        for (int v = 0; v < ND + 2; ++v) u[v * g.vs + c[side]] = (T)fma_(corr[side][v], idq, (double)x[side][v]);
 }
 
 struct RefluxSet {
@@ -108,6 +116,7 @@ __device__ __forceinline__ void restrict_cell(T *parent, const Grid &pg, const B
 {
     const int64_t pc = at(pg, b.lo[0] + i, b.lo[1] + j, b.lo[2] + k);
     constexpr int NC = 1 << ND;
+    T mean[ND + 2];  // (stored together: each store would hold up the next variable's loads)
 #pragma unroll
     for (int v = 0; v < ND + 2; ++v) {
         double sum = 0.0;
@@ -118,8 +127,10 @@ __device__ __forceinline__ void restrict_cell(T *parent, const Grid &pg, const B
             const int ck = ND > 2 ? FMR_NG + 2 * k + ((o >> 2) & 1) : 0;
             sum += (double)child[v * cg.vs + at(cg, ci, cj, ck)];
         }
-        parent[v * pg.vs + pc] = (T)(sum / (double)NC);
+        mean[v] = (T)(sum / (double)NC);
     }
+#pragma unroll
+    for (int v = 0; v < ND + 2; ++v) parent[v * pg.vs + pc] = mean[v];
 }
 
 // The replacement and the restriction of one child box in one launch: the
@@ -144,12 +155,11 @@ __global__ void __launch_bounds__(FB) k_reflux_restrict(T *u, Grid g, Box b, Ref
             if (q == 2) reflux_faces<ND, 2>(u, g, b, t, r.c[2][0], r.c[2][1], r.f[2][0], r.f[2][1], r.idq[2]);
         return;
     }
-    const int64_t cell = (int64_t)(bid - ND * rblocks) * FB + threadIdx.x;
-    const int64_t nxy = (int64_t)b.n[0] * b.n[1];
-    if (cell >= nxy * b.n[2]) return;
-    const int k = (int)(cell / nxy);
-    const int rem = (int)(cell - (int64_t)k * nxy);
-    const int j = rem / b.n[0], i = rem - j * b.n[0];
+    const unsigned cell = (unsigned)(bid - ND * rblocks) * FB + threadIdx.x;  // (a level's array is below 4 GiB)
+    const unsigned row = cell / (unsigned)b.n[0];
+    const int i = (int)(cell - row * (unsigned)b.n[0]);
+    const int k = ND < 3 ? 0 : (int)(row / (unsigned)b.n[1]), j = (int)row - k * b.n[1];
+    if (ND == 3 ? k >= b.n[2] : j >= b.n[1]) return;
     restrict_cell<ND>(u, g, b, child, cg, i, j, k);
 }
 
@@ -241,8 +251,7 @@ __global__ void __launch_bounds__(64) k_clock(FmrClock *c, int op0, int l0, int 
                                                unsigned long long *rate_bits, double cfl, double dt_fixed)
 {
     if (threadIdx.x != 0) return;
-    clock_op(c, op0, l0, nlev, rate_bits, cfl, dt_fixed);
-    clock_op(c, op1, l1, nlev, rate_bits, cfl, dt_fixed);
+    clock_ops(c, op0, l0, op1, l1, nlev, rate_bits, cfl, dt_fixed);
 }
 
 }  // namespace
@@ -279,7 +288,7 @@ hipError_t launch_prolong(T *fine, T *fine2, const Grid &fg, const T *parent, co
 {
     (void)gamma;
     RideJob<T> j = prolong_job<T>(fine, fine2, fg, parent, pg, parent_box, ndim, gm1, ck);
-    j.blocks = std::max(1, (j.cells + SB - 1) / SB);
+    j.blocks = std::max(1, ride_blocks(j, SB));
     const dim3 grid((unsigned)j.blocks);
     if (ndim == 1) hipLaunchKernelGGL((k_prolong<1, T>), grid, dim3(SB), 0, s, j);
     else if (ndim == 2) hipLaunchKernelGGL((k_prolong<2, T>), grid, dim3(SB), 0, s, j);
@@ -329,7 +338,7 @@ hipError_t launch_reflux_restrict(T *u, const Grid &g, const Box &child_box, int
     RideJob<T> j{};
     if (ride) {
         j = *ride;
-        j.blocks = (j.cells > 0 || j.ck.c) ? std::max(1, (j.cells + FB - 1) / FB) : 0;
+        j.blocks = ride_blocks(j, FB);
     }
     const int64_t blocks = rcblocks + j.blocks;
     if (blocks > INT32_MAX) return hipErrorInvalidValue;

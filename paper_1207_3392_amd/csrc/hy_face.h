@@ -299,6 +299,12 @@ __device__ __forceinline__ void box_faces(const T *u, const Grid &g, const Box &
     const int t1 = t % b.n[R1], t2 = t / b.n[R1];
     {
         const int f = side == 0 ? b.lo[Q] : b.lo[Q] + b.n[Q];  // face between cells f - 1 and f
+        // the accumulators' values under way with the cells' (read one by one
+        // between the stores, each would wait for the one before)
+        double *acc = side == 0 ? acc_lo : acc_hi;
+        double old[ND + 2];
+#pragma unroll
+        for (int v = 0; v < ND + 2; ++v) old[v] = assign ? 0.0 : acc[(int64_t)v * faces + t];
         T w4[4][ND + 2];
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
@@ -316,12 +322,8 @@ __device__ __forceinline__ void box_faces(const T *u, const Grid &g, const Box &
             wr[v] = fma_(-lim.hs, slope_mm(w4[1][v], w4[2][v], w4[3][v], lim.k), w4[2][v]);
         }
         face_flux<ND, Q, SOLVER>(wl, wr, fl, sqrt_gamma(gamma), inv_gm1, false);
-        double *acc = side == 0 ? acc_lo : acc_hi;
 #pragma unroll
-        for (int v = 0; v < ND + 2; ++v) {
-            double &a = acc[(int64_t)v * faces + t];
-            a = fma_(w, (double)fl[v], assign ? 0.0 : a);
-        }
+        for (int v = 0; v < ND + 2; ++v) acc[(int64_t)v * faces + t] = fma_(w, (double)fl[v], old[v]);
     }
 }
 

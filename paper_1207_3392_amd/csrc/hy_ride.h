@@ -66,28 +66,64 @@ __device__ __forceinline__ void shell_cell(const Grid &g, int s, int (&c)[3])
     }
 }
 
-__device__ __forceinline__ void clock_op(FmrClock *c, int op, int l, int nlev, unsigned long long *rate_bits,
-                                         double cfl, double dt_fixed)
+// Clock update op on level l, whose entry is a (and level l + 1's is n): the
+// new entry in a and in memory.  rb: the largest rate (CLOCK_DEEPEST).
+__device__ __forceinline__ void clock_op(FmrClock *c, int op, int l, FmrClock &a, const FmrClock &n,
+                                         unsigned long long rb, double cfl, double dt_fixed)
 {
     switch (op) {
-    case CLOCK_RESET:
+    case CLOCK_DEEPEST:
+    case CLOCK_DEEPEST_KEEP:
+        a.dt = dt_fixed > 0.0 ? dt_fixed : cfl / __longlong_as_double((long long)rb);
+        c[l].dt = a.dt;
+        break;
+    case CLOCK_COARSE:
+        a.dt = n.t - a.t;
+        c[l].dt = a.dt;
+        break;
+    case CLOCK_PROVISIONAL:
+        a.dtp = n.t - a.t;
+        c[l].dtp = a.dtp;
+        break;
+    case CLOCK_ADVANCE:
+        a.t += a.dt;
+        c[l].t = a.t;
+        break;
+    default: break;
+    }
+}
+
+// Up to two clock updates in order (op < 0: none), by one thread.  Everything
+// that they read is fetched at once: one memory latency, not one per value,
+// since the launch that carries them waits for this thread.
+__device__ __forceinline__ void clock_ops(FmrClock *c, int op0, int l0, int op1, int l1, int nlev,
+                                          unsigned long long *rate_bits, double cfl, double dt_fixed)
+{
+    auto reset = [&]() {
         for (int i = 0; i < nlev; ++i) c[i].t = 0.0;
         for (int k = 0; k < FMR_RATE_SLOTS; ++k) rate_bits[k * RATE_STRIDE] = 0ull;
-        break;
-    case CLOCK_DEEPEST:
-    case CLOCK_DEEPEST_KEEP: {
-        unsigned long long rb = 0ull;
-        for (int k = 0; k < FMR_RATE_SLOTS; ++k) {
-            rb = rb > rate_bits[k * RATE_STRIDE] ? rb : rate_bits[k * RATE_STRIDE];
-            if (op == CLOCK_DEEPEST) rate_bits[k * RATE_STRIDE] = 0ull;
-        }
-        c[l].dt = dt_fixed > 0.0 ? dt_fixed : cfl / __longlong_as_double((long long)rb);
-        break;
+    };
+    if (op0 == CLOCK_RESET) reset();
+    auto entry = [&](int l) { return l >= 0 && l < nlev ? c[l] : FmrClock{}; };
+    FmrClock a0 = entry(l0), n0 = entry(l0 + 1), a1 = entry(l1), n1 = entry(l1 + 1);
+    const bool d0 = op0 == CLOCK_DEEPEST || op0 == CLOCK_DEEPEST_KEEP;
+    const bool d1 = op1 == CLOCK_DEEPEST || op1 == CLOCK_DEEPEST_KEEP;
+    unsigned long long rb = 0ull;
+    if (d0 || d1) {
+        unsigned long long r[FMR_RATE_SLOTS];
+#pragma unroll
+        for (int k = 0; k < FMR_RATE_SLOTS; ++k) r[k] = rate_bits[k * RATE_STRIDE];
+#pragma unroll
+        for (int k = 0; k < FMR_RATE_SLOTS; ++k) rb = rb > r[k] ? rb : r[k];
+        if (op0 == CLOCK_DEEPEST || op1 == CLOCK_DEEPEST)
+            for (int k = 0; k < FMR_RATE_SLOTS; ++k) rate_bits[k * RATE_STRIDE] = 0ull;
     }
-    case CLOCK_COARSE: c[l].dt = c[l + 1].t - c[l].t; break;
-    case CLOCK_PROVISIONAL: c[l].dtp = c[l + 1].t - c[l].t; break;
-    case CLOCK_ADVANCE: c[l].t += c[l].dt; break;
-    default: break;
+    if (op0 >= 0) clock_op(c, op0, l0, a0, n0, rb, cfl, dt_fixed);
+    if (op1 >= 0) {
+        if (op0 >= 0 && l1 == l0) a1 = a0;
+        if (op0 >= 0 && l1 + 1 == l0) n1 = a0;
+        clock_op(c, op1, l1, a1, n1, rb, cfl, dt_fixed);
+        if (op1 == CLOCK_RESET) reset();
     }
 }
 
@@ -146,16 +182,27 @@ __device__ __forceinline__ void prolong_cell(const RideJob<T> &j, int sc)
     }
 }
 
-// Workgroup wg (of j.blocks, nthreads threads each) of a riding job: the
-// clock updates on its first thread, then its share of the shell cells.
+// Host: the workgroups (of nt threads) that a riding job takes: its shell
+// cells', and one for the clock, so that neither waits for the other.
+template <typename T>
+inline int ride_blocks(const RideJob<T> &j, int nt)
+{
+    return (j.cells + nt - 1) / nt + (j.ck.c ? 1 : 0);
+}
+
+// Workgroup wg (of j.blocks, nthreads threads each) of a riding job: the last
+// one carries out the clock updates if there are any, the others the shell
+// cells.
 template <int ND, typename T>
 __device__ __forceinline__ void ride_run(const RideJob<T> &j, int wg, int tid, int nthreads)
 {
-    if (wg == 0 && tid == 0 && j.ck.c) {
-        clock_op(j.ck.c, j.ck.op0, j.ck.l0, j.ck.nlev, j.ck.rate, j.ck.cfl, j.ck.dt_fixed);
-        clock_op(j.ck.c, j.ck.op1, j.ck.l1, j.ck.nlev, j.ck.rate, j.ck.cfl, j.ck.dt_fixed);
+    const int nb = j.blocks - (j.ck.c ? 1 : 0);
+    if (wg >= nb) {
+        if (tid == 0 && j.ck.c)
+            clock_ops(j.ck.c, j.ck.op0, j.ck.l0, j.ck.op1, j.ck.l1, j.ck.nlev, j.ck.rate, j.ck.cfl, j.ck.dt_fixed);
+        return;
     }
-    for (int sc = wg * nthreads + tid; sc < j.cells; sc += j.blocks * nthreads) prolong_cell<ND>(j, sc);
+    for (int sc = wg * nthreads + tid; sc < j.cells; sc += nb * nthreads) prolong_cell<ND>(j, sc);
 }
 
 }  // namespace

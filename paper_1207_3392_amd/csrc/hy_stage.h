@@ -151,8 +151,7 @@ hipError_t stage_extra_blocks(StageArgs<T> &a, int nt, int64_t *blocks)
         a.nbfwg = a.bf.nbox * ND * 2 * a.bf.blocks;
         *blocks += a.nbfwg;
     }
-    const int rb = (a.ride.cells + nt - 1) / nt;
-    a.ride.blocks = (a.ride.cells > 0 || a.ride.ck.c) ? (rb > 1 ? rb : 1) : 0;
+    a.ride.blocks = ride_blocks(a.ride, nt);
     *blocks += a.ride.blocks;
     return hipSuccess;
 }
