@@ -134,6 +134,16 @@ __global__ void __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) k_strip(const Sta
     T L[NP], d[NP], Flo[NP];
     T um[NP];
     T wb[NP];  // switch: the row below the current one
+    // stage 2: the row of U^n, fetched a row ahead (fetched at its use's row,
+    // the last of a row's work waited for it: 7 levels of 256^2 23.2 -> 22.1 ms)
+    T u0[NP];
+    auto load0 = [&](int r) {
+        bool f = false;
+        const unsigned ro = rowoff(r, f);
+#pragma unroll
+        for (int v = 0; v < NP; ++v) u0[v] = at(a.u0 + v * a.vstride, ro);
+    };
+    if constexpr (STAGE == 2) load0(y0);
     load(y0, UA);
     load(y0 - 1, um);
     {
@@ -196,13 +206,8 @@ __global__ void __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) k_strip(const Sta
     // primitives go to W2); the rows' registers are rotated by the caller
     auto body = [&](int r, T (&W0)[NP], T (&W1)[NP], T (&W2)[NP], T (&U0)[NP], T (&U1)[NP], T (&U2)[NP]) {
         (void)U1;
-        T u0[NP];
         bool nf = false;
         const unsigned ro = rowoff(r, nf);
-        if constexpr (STAGE == 2) {
-#pragma unroll
-            for (int v = 0; v < NP; ++v) u0[v] = at(a.u0 + v * a.vstride, ro);
-        }
         prim(r + 2, U2, W2);
         // ---- y face r + 1/2 ----
         T s[NP], R[NP], Fhi[NP];
@@ -275,6 +280,8 @@ __global__ void __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) k_strip(const Sta
         for (int v = 0; v < NP; ++v) out[v] += STAGE == 1 ? U0[v] : u0[v];
         // the row three ahead, into the registers this row leaves
         if (r + 3 <= y1 + 1) load(r + 3, U0);
+        if constexpr (STAGE == 2)
+            if (r + 1 < y1) load0(r + 1);
         if (own) {
 #pragma unroll
             for (int v = 0; v < NP; ++v) *(T *)((char *)(a.uout + v * a.vstride) + ro + xoff) = out[v];
