@@ -301,13 +301,12 @@ __global__ void __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) k_strip(const Sta
     }
     if (bad) atomicOr(&a.ctl->err, 1u);
     if constexpr (STAGE == 2) {
-        double m = (double)rate;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
+        double m = (double)lanes_max(rate);
         if (lane == 0) sRate[tid >> 6] = m;
         __syncthreads();
         if (tid == 0) {
-            for (int w = 1; w < wpw; ++w) m = fmax(m, sRate[w]);
+#pragma unroll
+            for (int w = 1; w < 8; ++w) m = fmax(m, w < wpw ? sRate[w] : 0.0);
             if (m > 0.0)
                 atomicMax(&a.ctl->rate[a.parity ^ 1][(blockIdx.x % RATE_SLOTS) * RATE_STRIDE],
                           (unsigned long long)__double_as_longlong(m));
