@@ -311,10 +311,35 @@ bool tile_supported(const hy_patch_desc &d, int bx, int by)
     return (bx == 64 && (by == 8 || by == 4)) || (bx == 32 && (by == 8 || (by == 16 && d.precision == 32)));
 }
 
+// Planes per workgroup of a 3D stage with `tiles` tiles in a plane of nz planes,
+// on a card that holds `slots` of its workgroups at once (256 CUs).  A workgroup
+// costs its planes and about two more for its ends, and the launch as many
+// workgroups in a row as there are rounds of slots, so what counts is
+// rounds (planes + 2): a last round that is nearly empty costs as much as a
+// full one.  Measured against "at least `slots` workgroups" (HLL 250 x 190 x
+// 310: 6 chunks, 576 workgroups for 512 slots): 5 chunks 4384 us against 5768,
+// 4 4834, 10 4472; FP64 150 x 140 x 130: 9 chunks 2885 against 3719 at 10, 13 2976,
+// 4 3053; switch 200 x 180 x 160: 9 chunks 3033 against 3490 at 10, 14 2957,
+// 4 3335; 256^3 stays at 4 (4711; 5 6270, 8 4843).  Between equals the shorter
+// chunks.  At most 64 planes and, where there are as many, at least 8.
+int z_chunk(int64_t tiles, int64_t nz, int64_t slots)
+{
+    const int64_t lo = (nz + 63) / 64, hi = std::max<int64_t>(lo, nz / 8);
+    int64_t best = nz, cost = INT64_MAX;
+    for (int64_t c = lo; c <= hi; ++c) {
+        const int64_t planes = (nz + c - 1) / c, used = (nz + planes - 1) / planes;
+        const int64_t v = (tiles * used + slots - 1) / slots * (planes + 2);
+        if (v <= cost) {
+            cost = v;
+            best = planes;
+        }
+    }
+    return (int)best;
+}
+
 void pick_config(hy_patch *p)
 {
-    // plane tile and z chunk: at least ~512 workgroups (two per CU) and at
-    // most 64 planes per workgroup (measured best at 256^3: 64x8 tile, 64 planes)
+    // plane tile (measured best at 256^3: 64x8) and z chunk
     const hy_patch_desc &d = p->d;
     const int64_t *n = p->padded ? p->inner : d.n;  // the extents the stages cover
     p->cfg.bx = 64;
@@ -331,11 +356,8 @@ void pick_config(hy_patch *p)
     }
     if (d.ndim == 3) {
         const int64_t tiles = ((n[0] + p->cfg.bx - 1) / p->cfg.bx) * ((n[1] + p->cfg.by - 1) / p->cfg.by);
-        int64_t chunks = (512 + tiles - 1) / tiles;
-        chunks = std::max<int64_t>(chunks, (n[2] + 63) / 64);
-        if (chunks > n[2] / 8) chunks = n[2] / 8;
-        if (chunks < 1) chunks = 1;
-        p->cfg.zchunk = (int)((n[2] + chunks - 1) / chunks);
+        // 512 threads a workgroup: two fit a CU in FP32, one in FP64
+        p->cfg.zchunk = z_chunk(tiles, n[2], d.precision == 32 ? 512 : 256);
         if (const char *e = std::getenv("HY_ZCHUNK")) {  // planes per workgroup, for tuning runs
             const int zc = std::atoi(e);
             if (zc >= 1 && zc <= n[2]) p->cfg.zchunk = zc;
@@ -345,13 +367,9 @@ void pick_config(hy_patch *p)
     }
     p->cfg_sw = p->cfg;
     if (d.ndim == 3 && d.precision == 32 && !std::getenv("HY_TILE")) {
-        // 32x8 tiles, three per CU: at least ~1536 workgroups (two rounds)
+        // 32x8 tiles, three per CU
         const int64_t tiles = ((n[0] + 31) / 32) * ((n[1] + 7) / 8);
-        int64_t chunks = (1536 + tiles - 1) / tiles;
-        chunks = std::max<int64_t>(chunks, (n[2] + 63) / 64);
-        if (chunks > n[2] / 8) chunks = n[2] / 8;
-        if (chunks < 1) chunks = 1;
-        p->cfg_sw = {32, 8, (int)((n[2] + chunks - 1) / chunks)};
+        p->cfg_sw = {32, 8, z_chunk(tiles, n[2], 768)};
         if (const char *e = std::getenv("HY_ZCHUNK")) {
             const int zc = std::atoi(e);
             if (zc >= 1 && zc <= n[2]) p->cfg_sw.zchunk = zc;
