@@ -318,8 +318,8 @@ bool tile_supported(const hy_patch_desc &d, int bx, int by)
 // rounds (planes + 2): a last round that is nearly empty costs as much as a
 // full one.  Measured against "at least `slots` workgroups" (HLL 250 x 190 x
 // 310: 6 chunks, 576 workgroups for 512 slots): 5 chunks 4384 us against 5768,
-// 4 4834, 10 4472; FP64 150 x 140 x 130: 9 chunks 2885 against 3719 at 10, 13 2976,
-// 4 3053; switch 200 x 180 x 160: 9 chunks 3033 against 3490 at 10, 14 2957,
+// 4 4834, 10 4472; FP64 150 x 140 x 130, 64x8 tiles: 9 chunks 2885 against 3719 at 10, 13
+// 2976, 4 3053; switch 200 x 180 x 160: 9 chunks 3033 against 3490 at 10, 14 2957,
 // 4 3335; 256^3 stays at 4 (4711; 5 6270, 8 4843).  Between equals the shorter
 // chunks.  At most 64 planes and, where there are as many, at least 8.
 int z_chunk(int64_t tiles, int64_t nz, int64_t slots)
@@ -339,10 +339,15 @@ int z_chunk(int64_t tiles, int64_t nz, int64_t slots)
 
 void pick_config(hy_patch *p)
 {
-    // plane tile (measured best at 256^3: 64x8) and z chunk
+    // Plane tile and z chunk.  FP32: 64x8, two workgroups per CU (256^3 4292 us
+    // per 10 steps against 5732 at 32x8, 200^3 2534 against 2800; 64^3 and 96 x 96
+    // x 300 as fast either way).  FP64 has registers for half as many threads:
+    // 32x8, again two per CU, one working while the other waits at a barrier
+    // (256^3 10510 us against 12489 at 64x8, 200^3 6300 / 7706, 128^3 1448 / 1594,
+    // 64^3 637 / 849, 150 x 140 x 130 2132 / 2871).
     const hy_patch_desc &d = p->d;
     const int64_t *n = p->padded ? p->inner : d.n;  // the extents the stages cover
-    p->cfg.bx = 64;
+    p->cfg.bx = d.ndim == 3 && d.precision == 64 ? 32 : 64;
     // (in 2D the tile only sets how many wavefronts share a workgroup: four
     // place more evenly on the CUs than eight)
     p->cfg.by = d.ndim == 1 ? 1 : (d.ndim == 2 ? 4 : 8);
@@ -356,8 +361,8 @@ void pick_config(hy_patch *p)
     }
     if (d.ndim == 3) {
         const int64_t tiles = ((n[0] + p->cfg.bx - 1) / p->cfg.bx) * ((n[1] + p->cfg.by - 1) / p->cfg.by);
-        // 512 threads a workgroup: two fit a CU in FP32, one in FP64
-        p->cfg.zchunk = z_chunk(tiles, n[2], d.precision == 32 ? 512 : 256);
+        // a CU holds 1024 threads in FP32, 512 in FP64 (registers)
+        p->cfg.zchunk = z_chunk(tiles, n[2], (d.precision == 32 ? 262144 : 131072) / (p->cfg.bx * p->cfg.by));
         if (const char *e = std::getenv("HY_ZCHUNK")) {  // planes per workgroup, for tuning runs
             const int zc = std::atoi(e);
             if (zc >= 1 && zc <= n[2]) p->cfg.zchunk = zc;
@@ -374,6 +379,12 @@ void pick_config(hy_patch *p)
             const int zc = std::atoi(e);
             if (zc >= 1 && zc <= n[2]) p->cfg_sw.zchunk = zc;
         }
+    }
+    if (d.ndim == 3 && d.precision == 64 && !std::getenv("HY_TILE") && !std::getenv("HY_ZCHUNK")) {
+        // the switch in FP64: 64x8, one per CU (256^3 20461 us per 10 steps against
+        // 21288 at 32x8, 128^3 2580 / 2853, 190 x 64 x 250 3848 / 4181; the other
+        // way round at 150 x 140 x 130, 4684 / 4244)
+        p->cfg_sw = {64, 8, z_chunk(((n[0] + 63) / 64) * ((n[1] + 7) / 8), n[2], 256)};
     }
 }
 
