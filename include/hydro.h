@@ -204,7 +204,7 @@ hy_status hy_kernel_config(hy_patch *p, char *buf, size_t len);
  * 32x16 in 2D and 3D, 64x1 in 1D; a patch starts with a shape picked from its
  * size (3D: FP32 64x8, FP64 32x8, with the chunks that fill whole rounds of the
  * card, at most 64 planes; 2D: 64x4).  The HLLC -> HLL switch keeps a shape of
- * its own (3D: FP32 32x8, FP64 64x8; else the same): hy_get_launch_cfg reports the
+ * its own (3D FP32: 32x8; else the same): hy_get_launch_cfg reports the
  * HLL/HLLC shape, hy_set_launch_cfg sets the shape of every solver,
  * hy_autotune the shape of the solver it tunes. */
 typedef struct {

@@ -344,7 +344,8 @@ void pick_config(hy_patch *p)
     // x 300 as fast either way).  FP64 has registers for half as many threads:
     // 32x8, again two per CU, one working while the other waits at a barrier
     // (256^3 10510 us against 12489 at 64x8, 200^3 6300 / 7706, 128^3 1448 / 1594,
-    // 64^3 637 / 849, 150 x 140 x 130 2132 / 2871).
+    // 64^3 637 / 849, 150 x 140 x 130 2132 / 2871; the switch 15869 / 20501, 9016 /
+    // 12729, 2246 / 2572, 1021 / 1327, 3288 / 4700).
     const hy_patch_desc &d = p->d;
     const int64_t *n = p->padded ? p->inner : d.n;  // the extents the stages cover
     p->cfg.bx = d.ndim == 3 && d.precision == 64 ? 32 : 64;
@@ -379,12 +380,6 @@ void pick_config(hy_patch *p)
             const int zc = std::atoi(e);
             if (zc >= 1 && zc <= n[2]) p->cfg_sw.zchunk = zc;
         }
-    }
-    if (d.ndim == 3 && d.precision == 64 && !std::getenv("HY_TILE") && !std::getenv("HY_ZCHUNK")) {
-        // the switch in FP64: 64x8, one per CU (256^3 20461 us per 10 steps against
-        // 21288 at 32x8, 128^3 2580 / 2853, 190 x 64 x 250 3848 / 4181; the other
-        // way round at 150 x 140 x 130, 4684 / 4244)
-        p->cfg_sw = {64, 8, z_chunk(((n[0] + 63) / 64) * ((n[1] + 7) / 8), n[2], 256)};
     }
 }
 

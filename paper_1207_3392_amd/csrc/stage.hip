@@ -1,5 +1,5 @@
-// stage.hip -- one Runge-Kutta stage of the finite-volume update, fused into
-// a single gfx950 kernel.
+// stage.hip -- one Runge-Kutta stage of the finite-volume update in 3D and 1D,
+// fused into a single gfx950 kernel (2D: strip.hip).
 //
 // Per cell the kernel performs, in the paper's order (Sec. 3, Alg. 1):
 // primitive recovery (Sec. 3.5), ghost values by index mapping (the boundary
@@ -66,13 +66,17 @@ __device__ __forceinline__ T learned_slope(const StageArgs<T> &a, int q, int v, 
     return sgn * (T)base[c];
 }
 
-// At least 4 waves per SIMD: the LDS plane tile admits two 512-thread
+// FP32, at least 4 waves per SIMD: the LDS plane tile admits two 512-thread
 // workgroups per CU, so registers beyond 128 per lane would only cost occupancy.
 template <int ND, typename T, int SOLVER, int STAGE, int LIM, int BX, int BY>
 // 512-thread tiles: four waves per SIMD (two workgroups per CU); 256-thread
 // tiles: three, which leaves the 3D kernels room to prefetch without spilling
-// (their LDS would allow four workgroups, but the registers then spill)
-__global__ void __launch_bounds__(BX *BY, (BX * BY == 256) ? 3 : 4) k_stage(const StageArgs<T> a)
+// (their LDS would allow four workgroups, but the registers then spill).  The
+// switch in FP64: two, as many as its LDS allows, which lets its 253 registers
+// fit (256^3 15869 us per 10 steps against 21288 with 168; HLL and HLLC are 3 to
+// 5 % faster with 168, 10510 against 10866).
+__global__ void __launch_bounds__(BX *BY, sizeof(T) == 8 && SOLVER == SOLVER_HLLC_SWITCH ? 2 : (BX * BY == 256) ? 3 : 4)
+    k_stage(const StageArgs<T> a)
 {
     constexpr int NP = ND + 2;
     constexpr int IP = ND + 1;
@@ -454,18 +458,12 @@ __global__ void __launch_bounds__(BX *BY, (BX * BY == 256) ? 3 : 4) k_stage(cons
                 sSx[v][ty][tx + 1] = lsx[v];
                 if constexpr (ND >= 2) sSy[v][ty + 1][tx] = lsy[v];
             }
-            // ring slope of cell (rx, ry): direct inside the domain, boundary
-            // mapped for a ghost (in 3D the extra code path costs more
-            // registers than the index arithmetic it saves: measured)
+            // ring slope of cell (rx, ry), boundary mapped (a direct path for
+            // the cells inside the domain costs more registers in 3D than the
+            // index arithmetic it saves: measured)
             auto ring_slope = [&](int q, int rx, int ry, T (&out)[NP]) {
-                if (ND < 3 && rx >= 0 && rx < nx && ry >= 0 && ry < ny) {
-                    const unsigned o = zko + (unsigned)(ry * nx + rx);
 #pragma unroll
-                    for (int v = 0; v < NP; ++v) out[v] = (T)at(a.slopes + (int64_t)(q * NP + v) * a.vstride, o);
-                } else {
-#pragma unroll
-                    for (int v = 0; v < NP; ++v) out[v] = learned_slope<ND>(a, q, v, rx, ry, kz);
-                }
+                for (int v = 0; v < NP; ++v) out[v] = learned_slope<ND>(a, q, v, rx, ry, kz);
             };
             if constexpr (ND >= 2) {
                 if (tid < 2 * BX) {
@@ -551,10 +549,9 @@ __global__ void __launch_bounds__(BX *BY, (BX * BY == 256) ? 3 : 4) k_stage(cons
             }
         };
         // waves that also carry ring items run at raised priority so the
-        // barrier that ends the phase is reached sooner
+        // barrier that ends the phase is reached sooner (3D: measured 5 %
+        // faster at 256^3)
         const int wv = tid >> 6;
-        // (3D only: measured 5 % faster at 256^3; the single-plane 2D blocks
-        // gain nothing)
         const bool ring1 = ND == 3 && (wv < (2 * BX + 63) / 64 || wv >= (NT - 2 * BY) / 64 ||
                                        (SW && wv >= RING0 / 64 && wv < (RING0 + NRING + 63) / 64));
         const bool ring2 = ND == 3 && (wv < (BX + 63) / 64 || wv >= (NT - BY) / 64);
