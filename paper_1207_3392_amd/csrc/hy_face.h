@@ -37,20 +37,21 @@ template <> __device__ __forceinline__ double rcp_<double>(double x)
     return fma_(fma_(-x, r, 1.0), r, r);
 }
 
-// sqrt(p / r), evaluated as p rsqrt(p r).  FP64: the hardware's reciprocal
-// root and one Newton step give y = 1 / sqrt(p r) to about 2^-45 and s = p y;
-// the residual p - s^2 r, with s r carried in two parts, then corrects s to
-// the last rounding: 12 instructions where a division and a root take 25.
+// sqrt(p / r), evaluated as p rsqrt(p r).  FP64: y = 1 / sqrt(p r) from the
+// hardware's reciprocal roots of p and of r, not of p r, which leaves the range
+// long before the ratio does (densities and pressures near 1e-155 or 1e155); one
+// Newton step on s = p y, with 1 - p r y^2 formed from p y and r y, leaves about
+// 2^-42, and the residual p - s^2 r, with s r carried in two parts, corrects s to
+// the last rounding: 14 instructions where a division and a root take 25.  (One
+// reciprocal root of p r saves 1 to 3 % of an FP64 step, 150 x 140 x 130, 10 steps:
+// 2168 us against 2202, and gives a NaN where p r overflows or vanishes.)
 __device__ __forceinline__ float root_ratio(float p, float r) { return p * __builtin_amdgcn_rsqf(p * r); }
 __device__ __forceinline__ double root_ratio(double p, double r)
 {
-    const double q = p * r;
-    double y = __builtin_amdgcn_rsq(q);
-    const double h = 0.5 * y;
-    y = fma_(fma_(-q * y, y, 1.0), h, y);
-    const double s = p * y, t = s * r;
+    const double y = __builtin_amdgcn_rsq(p) * __builtin_amdgcn_rsq(r), h = 0.5 * y, u = p * y;
+    const double s = fma_(fma_(-u, r * y, 1.0), 0.5 * u, u), t = s * r;
     const double e = fma_(-fma_(s, r, -t), s, fma_(-t, s, p));
-    return fma_(e, 0.5 * y, s);
+    return fma_(e, h, s);
 }
 
 // sqrt(p / rho), the sound speed divided by sqrt(gamma); the solvers fold
