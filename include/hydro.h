@@ -188,7 +188,9 @@ hy_status hy_set_mlp(hy_patch *p, const float *weights, size_t n);
 /* Per-kernel timing with HIP events on the patch stream (off by default).
  * While on, each stage launch is bracketed by events; hy_kernel_times
  * synchronises and returns the summed milliseconds and launch counts of the
- * first and second stage kernels since the last reset, then resets them. */
+ * first and second stage kernels since the last reset, then resets them.
+ * While on, a 1D patch whose runs of steps take one launch otherwise takes the
+ * two stage launches of every step, with the same results bit for bit. */
 hy_status hy_set_timing(hy_patch *p, int on);
 hy_status hy_kernel_times(hy_patch *p, double ms[2], int64_t launches[2]);
 

@@ -164,7 +164,7 @@ __global__ void __launch_bounds__(64 * NW) k_batch(const TubeDesc *__restrict__ 
         auto slot = [&](int r, unsigned tag) -> unsigned long long * {
             return mail + ((int64_t)(it.slot + r) * 2 + (tag & 1u)) * MAIL_WORDS;
         };
-        Line<float, SOLVER, NW, CPW> ln;
+        Line<float, SOLVER, NW, CPW, false> ln;
         ln.init(nl, d.bclo, d.bchi, hasl, hasr, d.gamma, d.gamma - 1.f, 1.f / (d.gamma - 1.f), d.theta, d.idx);
         float rate = 0.f;
 #pragma unroll
@@ -273,7 +273,7 @@ __global__ void __launch_bounds__(64 * NW) k_batch(const TubeDesc *__restrict__ 
 #pragma unroll
             for (int k = 0; k < CPW; ++k) {
                 if (wave + k * NW >= ln.nch) break;
-                rate = fmaxf(rate, ln.finish(k, D[k], c1, 0.f));
+                rate = fmaxf(rate, ln.finish(k, D[k], c1, 0.f, 0.5f * c1, 0.f));
                 __builtin_amdgcn_sched_barrier(0);
             }
             t += dt;

@@ -55,8 +55,12 @@ __device__ __forceinline__ double lane_value(double x, int l)
     return __longlong_as_double((long long)lane_u64((unsigned long long)__double_as_longlong(x), l));
 }
 
-// NW wavefronts with CPW chunks each (chunk c = wave + k NW).
-template <typename T, int SOLVER, int NW, int CPW>
+// NW wavefronts with CPW chunks each (chunk c = wave + k NW).  PATCH: rounds a
+// step as the 1D stage kernel (stage.hip) does, bit for bit, so that a patch's
+// results do not depend on which of the two takes a step.  (The tubes' own
+// order of operations rounds the second stage's change before it is added; a
+// run of some 13,000 steps amplifies the difference to 5e-5, so they keep it.)
+template <typename T, int SOLVER, int NW, int CPW, bool PATCH>
 struct Line {
     T U[CPW][3];    // the lane's cell of each chunk
     int from[CPW];  // LDS word of the lane's copy (-1: an own cell, a wall ghost or unused)
@@ -198,30 +202,33 @@ struct Line {
         flux_difference(w, D);
     }
     // the rest of the step from stage 1's flux differences; c1 = dt / dx, ca =
-    // dt a (uniform acceleration); returns the CFL rate of the new own cell
-    __device__ __forceinline__ T finish(int q, const T (&D)[3], T c1, T ca)
+    // dt a (uniform acceleration), c2 and cb the same of dt / 2; returns the
+    // CFL rate of the new own cell
+    __device__ __forceinline__ T finish(int q, const T (&D)[3], T c1, T ca, T c2, T cb)
     {
         T V[3], w[3], E[3];
 #pragma unroll
         for (int v = 0; v < 3; ++v) V[v] = fma_(c1, D[v], U[q][v]);
         if (ca != T(0)) {
             V[1] = fma_(U[q][0], ca, V[1]);
-            V[2] = fma_(U[q][1], ca, V[2]);
+            V[2] += U[q][1] * ca;
         }
         prims(q, V, w);
         flux_difference(w, E);
-        const T c2 = T(0.5) * c1, cb = T(0.5) * ca;
 #pragma unroll
-        for (int v = 0; v < 3; ++v) U[q][v] = fma_(T(0.5), U[q][v] + V[v], c2 * E[v]);
-        if (ca != T(0)) {
+        for (int v = 0; v < 3; ++v) {
+            if constexpr (PATCH) U[q][v] = fma_(c2, E[v], T(0.5) * (U[q][v] + V[v]));
+            else U[q][v] = fma_(T(0.5), U[q][v] + V[v], c2 * E[v]);
+        }
+        if (cb != T(0)) {
             U[q][1] = fma_(V[0], cb, U[q][1]);
-            U[q][2] = fma_(V[1], cb, U[q][2]);
+            U[q][2] += V[1] * cb;
         }
         return rate(q);
     }
     __device__ __forceinline__ T speed(const T (&w)[3]) const  // |v| + c
     {
-        if constexpr (sizeof(T) == 4) {
+        if constexpr (!PATCH && sizeof(T) == 4) {
             const T gp = gamma * w[2];
             return fma_(gp, __builtin_amdgcn_rsqf(w[0] * gp), fabs(w[1]));
         }

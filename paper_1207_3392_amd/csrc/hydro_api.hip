@@ -239,7 +239,8 @@ hipError_t one_step(hy_patch *p, int solver, int dt_mode, double dt, double cfl,
 }
 
 // 1D patches that one workgroup steps faster than two launches per step do.
-// (With timing on the stages are launched one by one, so that they can be timed.)
+// (With timing on the stages are launched one by one, so that they can be timed;
+// the two round alike, bit for bit.)
 bool takes_line(const hy_patch *p)
 {
     return p->d.ndim == 1 && !p->padded && p->d.limiter == HY_LIM_THETA && (!p->timing || p->capturing) &&

@@ -19,7 +19,7 @@ __global__ void __launch_bounds__(64 * NW) k_line(const StageArgs<T> a, int nste
     __shared__ T sEdge[2][(NW * CPW + 1) * LINE_EDGE];
     __shared__ T sRate[2][NW];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    Line<T, SOLVER, NW, CPW> ln;
+    Line<T, SOLVER, NW, CPW, true> ln;
     ln.init((int)a.n[0], a.bc[0][0], a.bc[0][1], false, false, a.gamma, a.gm1, a.inv_gm1, a.theta, a.idx[0]);
     T *u = a.uout;
 #pragma unroll
@@ -51,7 +51,9 @@ __global__ void __launch_bounds__(64 * NW) k_line(const StageArgs<T> a, int nste
             dt = fmin(a.cfl / rmax, a.t_end - t);
             if (!(dt > 0.0)) dt = 0.0;
         }
+        const T h = T(0.5) * (T)dt;
         const T c1 = uniform_((T)dt * a.idx[0]), ca = uniform_((T)dt * a.accel[0]);
+        const T c2 = uniform_(h * a.idx[0]), cb = uniform_(h * a.accel[0]);
         rate = T(0);
 #pragma unroll
         for (int k = 0; k < CPW; ++k) {
@@ -59,7 +61,7 @@ __global__ void __launch_bounds__(64 * NW) k_line(const StageArgs<T> a, int nste
             T D[3];
             ln.receive(k, edge);
             ln.stage1_flux(k, D);
-            rate = fmax(rate, ln.finish(k, D, c1, ca));
+            rate = fmax(rate, ln.finish(k, D, c1, ca, c2, cb));
             __builtin_amdgcn_sched_barrier(0);
         }
         t += dt;

@@ -136,3 +136,31 @@ def test_runs_longer_than_a_launch():
     assert np.array_equal(u, a.get_state()) and a.time() == pytest.approx(end, rel=1e-14)
     for p in (a, b, c):
         p.close()
+
+
+@pytest.mark.parametrize("prec", [32, 64])
+@pytest.mark.parametrize("solver", [hydro.HLL, hydro.HLLC])
+def test_timed_and_replayed_runs_equal_the_others(prec, solver):
+    """Per-kernel timing launches the stages one by one, a graph or a plain
+    call may take whole runs of steps in one launch: the same state, time and
+    next CFL step, bit for bit, of every patch."""
+    for n in (2, 57, 600, 2500):
+        for k, bc in enumerate(KINDS + ((1, 2),)):
+            pr = tube(n, bc, n + k)
+            pr.accel = (0.3 * (k % 2), 0.0, 0.0)
+            got = []
+            for how in ("plain", "timed", "graph", "one by one"):
+                p = hydro.Patch(pr, precision=prec)
+                p.set_timing(how == "timed")
+                if how == "graph":
+                    p.advance_graph(7, 0.4, solver=solver)
+                elif how == "one by one":
+                    for _ in range(7):
+                        p.advance(1, 0.4, solver=solver)
+                else:
+                    p.advance(7, 0.4, solver=solver)
+                p.step(0.5 * p.cfl_dt(0.4), solver)
+                got.append((p.get_state(hydro.CONSERVED), p.time(), p.cfl_dt(0.4)))
+                p.close()
+            for g in got[1:]:
+                assert np.array_equal(g[0], got[0][0]) and g[1:] == got[0][1:], (n, bc)
