@@ -51,9 +51,12 @@ __global__ void __launch_bounds__(64 * NW) k_line(const StageArgs<T> a, int nste
             dt = fmin(a.cfl / rmax, a.t_end - t);
             if (!(dt > 0.0)) dt = 0.0;
         }
-        const T h = T(0.5) * (T)dt;
-        const T c1 = uniform_((T)dt * a.idx[0]), ca = uniform_((T)dt * a.accel[0]);
-        const T c2 = uniform_(h * a.idx[0]), cb = uniform_(h * a.accel[0]);
+        const T c1 = uniform_((T)dt * a.idx[0]), c2 = T(0.5) * c1;
+        T ca = T(0), cb = T(0);
+        if (a.accel[0] != T(0)) {
+            ca = uniform_((T)dt * a.accel[0]);
+            cb = uniform_(T(0.5) * (T)dt * a.accel[0]);
+        }
         rate = T(0);
 #pragma unroll
         for (int k = 0; k < CPW; ++k) {
