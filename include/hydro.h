@@ -194,7 +194,9 @@ hy_status hy_set_mlp(hy_patch *p, const float *weights, size_t n);
 hy_status hy_set_timing(hy_patch *p, int on);
 hy_status hy_kernel_times(hy_patch *p, double ms[2], int64_t launches[2]);
 
-/* Name of the stage kernel configuration in use (for profiles). */
+/* Name and launch shape of the kernel that the patch's steps run in (for
+ * profiles): k_stage (3D, 1D), k_strip (2D; rows per wavefront) or k_line (1D,
+ * runs of steps in one launch). */
 hy_status hy_kernel_config(hy_patch *p, char *buf, size_t len);
 
 /* Launch shape of the stage kernels.  3D: a workgroup of bx x by threads owns

@@ -135,7 +135,9 @@ hipError_t launch_stage(int ndim, int solver, int stage, int limiter, const Laun
                         const StageArgs<T> &a, hipStream_t s);
 
 // The 2D stages (strip.hip), reached through launch_stage: cfg.bx * cfg.by
-// threads per workgroup.
+// threads per workgroup, strip_rows rows per wavefront (n: the cells updated).
+template <typename T>
+int strip_rows(const int64_t n[3]);
 template <typename T>
 hipError_t launch_strip(int solver, int stage, int limiter, const LaunchCfg &cfg, const StageArgs<T> &a, hipStream_t s);
 

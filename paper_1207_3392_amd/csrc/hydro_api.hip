@@ -764,8 +764,16 @@ hy_status hy_kernel_times(hy_patch *p, double ms[2], int64_t launches[2])
 hy_status hy_kernel_config(hy_patch *p, char *buf, size_t len)
 {
     if (!p || !buf || len == 0) return fail(HY_EINVAL, "null argument");
-    std::snprintf(buf, len, "k_stage<nd=%d,%s,tile=%dx%d> zchunk=%d", p->d.ndim, p->d.precision == 64 ? "f64" : "f32",
-                  p->cfg.bx, p->cfg.by, p->cfg.zchunk);
+    const hy_patch_desc &d = p->d;
+    const char *t = d.precision == 64 ? "f64" : "f32";
+    const int64_t *n = p->padded ? p->inner : d.n;
+    if (takes_line(p))
+        std::snprintf(buf, len, "k_line<nd=1,%s> threads=1024", t);
+    else if (d.ndim == 2)
+        std::snprintf(buf, len, "k_strip<nd=2,%s> threads=%d rows=%d", t, p->cfg.bx * p->cfg.by,
+                      d.precision == 64 ? hy::strip_rows<double>(n) : hy::strip_rows<float>(n));
+    else
+        std::snprintf(buf, len, "k_stage<nd=%d,%s,tile=%dx%d> zchunk=%d", d.ndim, t, p->cfg.bx, p->cfg.by, p->cfg.zchunk);
     return HY_OK;
 }
 

@@ -314,23 +314,34 @@ __global__ void __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) k_strip(const Sta
     }
 }
 
+}  // namespace
+
+// Rows per chunk: a short chunk repeats its 3 rows and one face more often, a
+// long one leaves few wavefronts to hide latency with.  Both costs balance where
+// the rows grow as the square root of the strips' total length (FP32,
+// 256-thread workgroups, us per step: 2048^2 77 / 72 / 75 at 6 / 12 / 24 rows,
+// 1024^2 30 / 28 / 32 at 3 / 5 / 8, 512^2 14.9 / 13.9 / 16.0 at 1 / 3 / 4, 256^2
+// 9.5 / 11.3 at 1 / 3; FP64 1024^2 76 / 61 / 86 at 3 / 10 / 16).
+template <typename T>
+int strip_rows(const int64_t n[3])
+{
+    const double len = std::sqrt((double)n[1] * (double)((n[0] + SC - 1) / SC));
+    int64_t rows = (int64_t)(len / (sizeof(T) == 4 ? 24.0 : 14.0) + 0.5);
+    rows = rows < 1 ? 1 : (rows > 32 ? 32 : rows);
+    return (int)(rows > n[1] ? n[1] : rows);
+}
+template int strip_rows<float>(const int64_t *);
+template int strip_rows<double>(const int64_t *);
+
+namespace {
+
 template <typename T, int SOLVER, int STAGE, int LIM>
 hipError_t launch_one(const LaunchCfg &cfg, StageArgs<T> a, hipStream_t s)
 {
     const int nt = cfg.bx * cfg.by, wpw = nt / 64;
     a.tiles_x = (int)((a.n[0] + SC - 1) / SC);
-    // Rows per chunk: a short chunk repeats its 3 rows and one face more
-    // often, a long one leaves few wavefronts to hide latency with.  Both
-    // costs balance where the rows grow as the square root of the strips'
-    // total length (FP32, 256-thread workgroups, us per step: 2048^2 77 / 72 /
-    // 75 at 6 / 12 / 24 rows, 1024^2 30 / 28 / 32 at 3 / 5 / 8, 512^2 14.9 /
-    // 13.9 / 16.0 at 1 / 3 / 4, 256^2 9.5 / 11.3 at 1 / 3; FP64 1024^2 76 / 61 /
-    // 86 at 3 / 10 / 16).
-    const double len = std::sqrt((double)a.n[1] * (double)a.tiles_x);
-    int64_t rows = (int64_t)(len / (sizeof(T) == 4 ? 24.0 : 14.0) + 0.5);
-    rows = rows < 1 ? 1 : (rows > 32 ? 32 : rows);
-    if (rows > a.n[1]) rows = a.n[1];
-    a.zchunk = (int)rows;
+    const int rows = strip_rows<T>(a.n);
+    a.zchunk = rows;
     a.tiles_y = (int)((a.n[1] + rows - 1) / rows);
     a.ntiles = (int)(((int64_t)a.tiles_x * a.tiles_y + wpw - 1) / wpw);
     int64_t blocks = a.ntiles;

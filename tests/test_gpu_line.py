@@ -164,3 +164,19 @@ def test_timed_and_replayed_runs_equal_the_others(prec, solver):
                 p.close()
             for g in got[1:]:
                 assert np.array_equal(g[0], got[0][0]) and g[1:] == got[0][1:], (n, bc)
+
+
+def test_kernel_config_names_the_kernel_that_runs():
+    def name(ndim, n, prec=32, timing=False):
+        p = hydro.Patch(wl.random_smooth_patch(ndim, n, seed=1), precision=prec)
+        p.set_timing(timing)
+        s = p.kernel_config()
+        p.close()
+        return s
+
+    for prec, t in ((32, "f32"), (64, "f64")):
+        assert name(1, (600,), prec) == f"k_line<nd=1,{t}> threads=1024"
+        assert name(1, (600,), prec, True) == f"k_stage<nd=1,{t},tile=64x1> zchunk=1"
+        assert name(1, (9000,), prec) == f"k_stage<nd=1,{t},tile=64x1> zchunk=1"
+        assert name(2, (70, 40), prec) == f"k_strip<nd=2,{t}> threads=256 rows=1"
+        assert name(3, (20, 12, 9), prec).startswith(f"k_stage<nd=3,{t},tile=")
