@@ -141,12 +141,11 @@ int strip_rows(const int64_t n[3]);
 template <typename T>
 hipError_t launch_strip(int solver, int stage, int limiter, const LaunchCfg &cfg, const StageArgs<T> &a, hipStream_t s);
 
-// nsteps whole steps of a 1D patch of at most line_max cells in one launch
+// nsteps whole steps of a 1D patch of at most LINE_CELLS cells in one launch
 // (line.hip): a as for a second stage (uout == u0 == U^n), generalised-minmod
-// limiter, HLL or HLLC; the time, the rate and the parity slot as nsteps
-// steps of the stage kernels leave them.
-template <typename T>
-constexpr int64_t line_max() { return sizeof(T) == 4 ? 96 * 56 : 64 * 56; }
+// limiter, HLL or HLLC; the state, the time, the rate and the parity slot as
+// nsteps steps of the stage kernels leave them, bit for bit.
+constexpr int64_t LINE_CELLS = 64 * 56;
 template <typename T>
 hipError_t launch_line(int solver, const StageArgs<T> &a, int nsteps, hipStream_t s);
 

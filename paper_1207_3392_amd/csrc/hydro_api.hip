@@ -238,28 +238,42 @@ hipError_t one_step(hy_patch *p, int solver, int dt_mode, double dt, double cfl,
     return e;
 }
 
-// 1D patches that one workgroup steps faster than two launches per step do.
-// (With timing on the stages are launched one by one, so that they can be timed;
-// the two round alike, bit for bit.)
-bool takes_line(const hy_patch *p)
+// Whether one launch of m steps on one workgroup (k_line) is the faster way for
+// a 1D patch than two stage launches a step.  Fits to measured times, us, n =
+// 600 .. 5376, HLL and HLLC: k_line takes 2.3 + 5e-4 n a launch and 0.65 + 1.85e-3 n
+// a step (FP64 2.3 + 6e-4 n, 0.9 + 3.7e-3 n), the stages 7.6 a step in a replayed graph
+// and 7.2 to 8.2 launched (FP64 8.6, 8.6 to 9.8).  So long runs take k_line up to
+// 3584 cells (3584: 7.0 to 7.15 against 7.5 in a graph, 8.2 launched; 4480: 8.9
+// against 7.5; FP64 1792: 6.9 to 7.3 against 8.6; 2200 HLLC: 8.9 against 8.7), single steps
+// up to some 1900 (FP64 1250; 1792: 6.7 against 7.3; 2200: 8.0 against 7.3; FP64 1344 8.4
+// against 8.7, 1792 10.1 against 8.8).
+// With timing on the stages are launched one by one, so that they can be timed;
+// the two round alike, bit for bit.
+bool takes_line(const hy_patch *p, int m)
 {
-    return p->d.ndim == 1 && !p->padded && p->d.limiter == HY_LIM_THETA && (!p->timing || p->capturing) &&
-           p->d.n[0] <= (p->d.precision == 64 ? hy::line_max<double>() : hy::line_max<float>());
+    if (p->d.ndim != 1 || p->padded || p->d.limiter != HY_LIM_THETA || (p->timing && !p->capturing)) return false;
+    if (p->d.n[0] > hy::LINE_CELLS) return false;
+    const double n = (double)p->d.n[0];
+    if (p->d.precision == 64) return 2.3 + 6e-4 * n + m * (0.9 + 3.7e-3 * n) <= m * 8.6;
+    return 2.3 + 5e-4 * n + m * (0.65 + 1.85e-3 * n) <= m * 7.6;
 }
+
+constexpr int kLineSteps = 4096;  // steps per launch at most: a launch stays within some 40 ms
 
 hipError_t steps(hy_patch *p, int nsteps, int solver, int dt_mode, double dt, double cfl, double t_end)
 {
-    constexpr int kMost = 4096;  // steps per launch: a launch stays within some 50 ms
-    const bool line = takes_line(p);
     const int sv = solver == HY_HLL ? HY_HLL : HY_HLLC;  // no transverse faces in 1D: the switch is HLLC
     hipError_t e = hipSuccess;
     for (int done = 0; done < nsteps && e == hipSuccess;) {
-        const int m = line ? std::min(kMost, nsteps - done) : 1;
-        if (!line) e = one_step(p, solver, dt_mode, dt, cfl, t_end);
-        else if (p->d.precision == 64)
-            e = hy::launch_line<double>(sv, stage_args<double>(p, 2, dt_mode, dt, cfl, t_end), m, p->stream);
-        else e = hy::launch_line<float>(sv, stage_args<float>(p, 2, dt_mode, dt, cfl, t_end), m, p->stream);
-        if (line && e == hipSuccess) p->parity ^= m & 1;
+        const int m = std::min(kLineSteps, nsteps - done);
+        if (takes_line(p, m)) {
+            if (p->d.precision == 64)
+                e = hy::launch_line<double>(sv, stage_args<double>(p, 2, dt_mode, dt, cfl, t_end), m, p->stream);
+            else e = hy::launch_line<float>(sv, stage_args<float>(p, 2, dt_mode, dt, cfl, t_end), m, p->stream);
+            if (e == hipSuccess) p->parity ^= m & 1;
+        } else {
+            for (int k = 0; k < m && e == hipSuccess; ++k) e = one_step(p, solver, dt_mode, dt, cfl, t_end);
+        }
         done += m;
     }
     return e;
@@ -767,13 +781,20 @@ hy_status hy_kernel_config(hy_patch *p, char *buf, size_t len)
     const hy_patch_desc &d = p->d;
     const char *t = d.precision == 64 ? "f64" : "f32";
     const int64_t *n = p->padded ? p->inner : d.n;
-    if (takes_line(p))
+    int m = 1;  // steps a call from which on k_line is taken
+    while (m < kLineSteps && !takes_line(p, m)) ++m;
+    char stage[64];
+    std::snprintf(stage, sizeof(stage), "k_stage<nd=%d,%s,tile=%dx%d> zchunk=%d", d.ndim, t, p->cfg.bx, p->cfg.by,
+                  p->cfg.zchunk);
+    if (m == 1)
         std::snprintf(buf, len, "k_line<nd=1,%s> threads=1024", t);
+    else if (m < kLineSteps)
+        std::snprintf(buf, len, "k_line<nd=1,%s> threads=1024 from %d steps a call, %s below", t, m, stage);
     else if (d.ndim == 2)
         std::snprintf(buf, len, "k_strip<nd=2,%s> threads=%d rows=%d", t, p->cfg.bx * p->cfg.by,
                       d.precision == 64 ? hy::strip_rows<double>(n) : hy::strip_rows<float>(n));
     else
-        std::snprintf(buf, len, "k_stage<nd=%d,%s,tile=%dx%d> zchunk=%d", d.ndim, t, p->cfg.bx, p->cfg.by, p->cfg.zchunk);
+        std::snprintf(buf, len, "%s", stage);
     return HY_OK;
 }
 

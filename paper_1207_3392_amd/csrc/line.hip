@@ -2,12 +2,16 @@
 // loop (dt from the device, both Runge-Kutta stages, the CFL rate of the new
 // state) on one workgroup, the state in registers (hy_line.h).
 //
-// What bounds it: the latency of one step's dependent instructions (1.8 us a
-// step up to about 500 cells), then the vector issue of one compute unit (2.0
-// us per 1000 cells).  Two stage launches per step cost 8.6 us in a replayed
-// graph and 10 us launched one by one, so one workgroup is the faster way up
-// to LINE_MAX cells; longer patches take the stage kernels over the whole
-// chip.
+// What bounds it: the latency of one step's dependent instructions (1.0 us a
+// step of 16 cells, 1.7 of 600), then the vector issue of one compute unit (1.85 us
+// per 1000 cells, FP64 3.7), and per launch the loads, the stores and the ends
+// (2.3 us and 0.5 us per 1000 cells).  us per step, HLLC, in runs of 400:
+//   cells               600  1000  1792  2700  3584  4480  5376
+//   FP32 here          1.71  2.55  3.71  5.80  7.15   9.0  10.6
+//   FP32 stage graph   7.72  7.71  7.69  7.77  7.59   7.6   7.6
+//   FP64 here          3.16  4.81  7.27  11.3  13.9
+//   FP64 stage graph   8.78  8.80  8.70  8.80  8.62
+// The host (takes_line) sends each run of steps to the faster of the two.
 #include "hy_line.h"
 
 namespace hy {
@@ -88,7 +92,7 @@ __global__ void __launch_bounds__(64 * NW) k_line(const StageArgs<T> a, int nste
     }
 }
 
-// Register footprints: 16, 32, 64 and (FP32) 96 chunks over 16 wavefronts.
+// Register footprints: 16, 32 and 64 chunks over 16 wavefronts.
 template <typename T, int SOLVER>
 hipError_t launch_sized(const StageArgs<T> &a, int nsteps, hipStream_t s)
 {
@@ -96,9 +100,7 @@ hipError_t launch_sized(const StageArgs<T> &a, int nsteps, hipStream_t s)
     const dim3 g(1), b(1024);
     if (nch <= 16) hipLaunchKernelGGL((k_line<T, SOLVER, 16, 1>), g, b, 0, s, a, nsteps);
     else if (nch <= 32) hipLaunchKernelGGL((k_line<T, SOLVER, 16, 2>), g, b, 0, s, a, nsteps);
-    else if (nch <= 64) hipLaunchKernelGGL((k_line<T, SOLVER, 16, 4>), g, b, 0, s, a, nsteps);
-    else if (sizeof(T) == 4 && nch <= 96) hipLaunchKernelGGL((k_line<float, SOLVER, 16, 6>), g, b, 0, s, *(const StageArgs<float> *)&a, nsteps);
-    else return hipErrorInvalidValue;
+    else hipLaunchKernelGGL((k_line<T, SOLVER, 16, 4>), g, b, 0, s, a, nsteps);
     return hipGetLastError();
 }
 
@@ -107,7 +109,7 @@ hipError_t launch_sized(const StageArgs<T> &a, int nsteps, hipStream_t s)
 template <typename T>
 hipError_t launch_line(int solver, const StageArgs<T> &a, int nsteps, hipStream_t s)
 {
-    if (nsteps < 1 || a.n[0] > line_max<T>() || a.uout != a.u0) return hipErrorInvalidValue;
+    if (nsteps < 1 || a.n[0] > LINE_CELLS || a.uout != a.u0) return hipErrorInvalidValue;
     return solver == SOLVER_HLL ? launch_sized<T, SOLVER_HLL>(a, nsteps, s) : launch_sized<T, SOLVER_HLLC>(a, nsteps, s);
 }
 

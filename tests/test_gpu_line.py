@@ -110,7 +110,8 @@ def test_patches_at_chunk_edges(prec, solver):
 
 @pytest.mark.parametrize("prec", [32, 64])
 def test_patches_around_the_longest_line(prec):
-    """The longest line and one cell more (which takes the stage kernels)."""
+    """Patches past the longest run of steps in one launch, where the stage
+    kernels take over (the two routes are compared bit for bit below)."""
     n = 5376 if prec == 32 else 3584
     for k in (0, 1):
         patch_case(n + k, wl.BC_REFLECT, hydro.HLLC, prec, 2)
@@ -180,3 +181,27 @@ def test_kernel_config_names_the_kernel_that_runs():
         assert name(1, (9000,), prec) == f"k_stage<nd=1,{t},tile=64x1> zchunk=1"
         assert name(2, (70, 40), prec) == f"k_strip<nd=2,{t}> threads=256 rows=1"
         assert name(3, (20, 12, 9), prec).startswith(f"k_stage<nd=3,{t},tile=")
+
+
+@pytest.mark.parametrize("prec", [32, 64])
+def test_route_of_a_run_changes_nothing(prec):
+    """Either side of the sizes and run lengths where a run of steps goes
+    from one launch to the stage kernels, against the timed run (which takes
+    the stage kernels): the same bits; and which of the two a size takes."""
+    t = f"f{prec}"
+    line, stage = f"k_line<nd=1,{t}> threads=1024", f"k_stage<nd=1,{t},tile=64x1> zchunk=1"
+    names = {32: {1792: line, 2500: line, 3584: line, 3585: stage, 5376: stage},
+             64: {896: line, 1792: line, 2200: stage, 3584: stage}}[prec]
+    for n in (896, 897, 1254, 1256, 1792, 1793, 1960, 2070, 2085, 2200, 2500, 3583, 3584, 3585, 5376):
+        pr = tube(n, wl.BC_REFLECT, n)
+        a, b = hydro.Patch(pr, precision=prec), hydro.Patch(pr, precision=prec)
+        b.set_timing(True)
+        if n in names:
+            assert a.kernel_config().startswith(names[n]), (n, a.kernel_config())
+        for m in (1, 2, 3, 5, 14, 40):
+            for p in (a, b):
+                p.advance(m, 0.4)
+        assert np.array_equal(a.get_state(), b.get_state()) and a.time() == b.time(), n
+        assert a.cfl_dt(0.4) == b.cfl_dt(0.4)
+        a.close()
+        b.close()
