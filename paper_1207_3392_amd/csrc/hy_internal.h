@@ -110,7 +110,7 @@ struct StageArgs {
     T gamma, gm1, inv_gm1, theta;
     T accel[3];
     int bc[3][2];
-    int zchunk;       // planes per block along z (3D)
+    int zchunk;       // planes per block along z (3D); 2D: rows per chunk (strip.hip)
     int tiles_x, tiles_y, ntiles;  // tile grid (set by the launcher)
     DevCtl *ctl;
     int parity;       // slot of the input state's time / rate

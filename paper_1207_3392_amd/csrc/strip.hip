@@ -23,12 +23,13 @@
 #include "hy_ride.h"
 #include "hy_stage.h"
 
-#include <cmath>
+#include <limits>
 
 namespace hy {
 namespace {
 
 constexpr int SC = 60;  // columns a wavefront updates: lanes 2 .. 61
+constexpr int COLS = 64;  // StageArgs::zchunk holds the rows per chunk (1 .. 32) and this flag: chunks fastest
 
 template <typename T, int SOLVER, int STAGE, int LIM>
 __global__ void __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) k_strip(const StageArgs<T> a)
@@ -52,7 +53,9 @@ __global__ void __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) k_strip(const Sta
     const int nx = (int)a.n[0], ny = (int)a.n[1];
     const int vx = PAD ? a.voff[0] : 0, vy = PAD ? a.voff[1] : 0;
     const int sx = PAD ? a.vm[0] : nx;
-    // each XCD takes a contiguous band of the strips' chunks (strips fastest)
+    // each XCD takes a contiguous band of the chunks: rows of them (strips
+    // fastest), or, in patches lying along x, columns, so that the rows that two
+    // chunks share come from one XCD's cache
     int wid;
     {
         const int lid = blockIdx.x, total = a.ntiles;
@@ -64,9 +67,12 @@ __global__ void __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) k_strip(const Sta
     // rows' loads and update nothing)
     const bool idle = wid >= a.tiles_x * a.tiles_y;
     if (idle) wid = a.tiles_x * a.tiles_y - 1;
-    const int chunk = wid / a.tiles_x, strip = wid - chunk * a.tiles_x;
-    const int y0 = chunk * a.zchunk;
-    const int y1 = idle ? y0 : (y0 + a.zchunk < ny ? y0 + a.zchunk : ny);
+    const int major = wid / a.tiles_x, minor = wid - major * a.tiles_x;
+    const bool cols = (a.zchunk & COLS) != 0;
+    const int rows = a.zchunk & (COLS - 1);
+    const int chunk = cols ? minor : major, strip = cols ? major : minor;
+    const int y0 = chunk * rows;
+    const int y1 = idle ? y0 : (y0 + rows < ny ? y0 + rows : ny);
 
     const T gamma = a.gamma, gm1 = a.gm1, igm1 = a.inv_gm1;
     const T sg = uniform_(sqrt_gamma(gamma));
@@ -317,18 +323,30 @@ __global__ void __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) k_strip(const Sta
 }  // namespace
 
 // Rows per chunk: a short chunk repeats its 3 rows and one face more often, a
-// long one leaves few wavefronts to hide latency with.  Both costs balance where
-// the rows grow as the square root of the strips' total length (FP32,
-// 256-thread workgroups, us per step: 2048^2 77 / 72 / 75 at 6 / 12 / 24 rows,
-// 1024^2 30 / 28 / 32 at 3 / 5 / 8, 512^2 14.9 / 13.9 / 16.0 at 1 / 3 / 4, 256^2
-// 9.5 / 11.3 at 1 / 3; FP64 1024^2 76 / 61 / 86 at 3 / 10 / 16).
+// long one leaves few wavefronts to hide latency with, and a last round over the
+// card's 1024 SIMDs that is nearly empty costs as much as a full one.  The rows
+// are those with the least (1.5 + k) (rows + 1.6), FP64 (0.7 + k) (rows + 2), k the
+// wavefronts on the busiest SIMD: over 54 shapes of 10^4 to 10^7 cells the step is
+// then within 2 % (FP64 7 %) of the best of 1 .. 32 rows, on average 0.2 % (0.8 %).
+// (Rows as the square root of the strips' length, picked before: 15 % and 31 %, on
+// average 2 and 11 %.  us per step, HLLC: FP32 700^2 20.6 -> 17.9, FP64 38.7 -> 30.3;
+// FP64 61 x 4000 32.4 -> 26.1; FP32 2048^2 75.8 and 512^2 14.2 as before.)
 template <typename T>
 int strip_rows(const int64_t n[3])
 {
-    const double len = std::sqrt((double)n[1] * (double)((n[0] + SC - 1) / SC));
-    int64_t rows = (int64_t)(len / (sizeof(T) == 4 ? 24.0 : 14.0) + 0.5);
-    rows = rows < 1 ? 1 : (rows > 32 ? 32 : rows);
-    return (int)(rows > n[1] ? n[1] : rows);
+    const int ny = (int)n[1], strips = (int)((n[0] + SC - 1) / SC);
+    const float a = sizeof(T) == 4 ? 1.5f : 0.7f, b = sizeof(T) == 4 ? 1.6f : 2.f;
+    int best = 1;
+    float cost = std::numeric_limits<float>::max();
+    for (int r = 1; r <= 32 && r <= ny; ++r) {
+        const int k = (strips * ((ny + r - 1) / r) + 1023) >> 10;
+        const float c = (a + (float)k) * ((float)r + b);
+        if (c < cost) {
+            cost = c;
+            best = r;
+        }
+    }
+    return best;
 }
 template int strip_rows<float>(const int64_t *);
 template int strip_rows<double>(const int64_t *);
@@ -339,11 +357,15 @@ template <typename T, int SOLVER, int STAGE, int LIM>
 hipError_t launch_one(const LaunchCfg &cfg, StageArgs<T> a, hipStream_t s)
 {
     const int nt = cfg.bx * cfg.by, wpw = nt / 64;
-    a.tiles_x = (int)((a.n[0] + SC - 1) / SC);
     const int rows = strip_rows<T>(a.n);
-    a.zchunk = rows;
-    a.tiles_y = (int)((a.n[1] + rows - 1) / rows);
-    a.ntiles = (int)(((int64_t)a.tiles_x * a.tiles_y + wpw - 1) / wpw);
+    const int strips = (int)((a.n[0] + SC - 1) / SC), chunks = (int)((a.n[1] + rows - 1) / rows);
+    // (FP32, us per step: 20,000 x 8 16.0 strips fastest, 11.6 chunks fastest; 10,000 x 30
+    // 17.5 / 14.9; 5000 x 32 13.6 / 11.8; 3000 x 100 15.2 / 15.2; 2000 x 16 9.2 / 9.4; 400^2 12.8 / 14.2)
+    const bool cols = a.n[0] >= 128 * a.n[1];
+    a.zchunk = rows | (cols ? COLS : 0);
+    a.tiles_x = cols ? chunks : strips;
+    a.tiles_y = cols ? strips : chunks;
+    a.ntiles = (int)(((int64_t)strips * chunks + wpw - 1) / wpw);
     int64_t blocks = a.ntiles;
     if constexpr (LIM == LIM_THETA_PADDED) {
         const hipError_t e = stage_extra_blocks<2>(a, nt, &blocks);

@@ -65,8 +65,9 @@ def test_strip_widths(prec, bc):
 @pytest.mark.parametrize("solver", [oracle.HLL, oracle.HLLC])
 @pytest.mark.parametrize("prec", [32, 64])
 def test_chunk_remainders(prec, solver):
-    """Chunks of 2 to 4 rows (3 strips of 1303 to 1306 rows), a last chunk of
-    every remainder, walls and gravity, both workgroup sizes."""
+    """Three strips of 1303 to 1306 rows in chunks of 2 rows (FP64 4), a last
+    chunk of every remainder, walls and gravity, both workgroup sizes (longer
+    chunks: test_rows_per_chunk)."""
     for ny, tile in ((1303, (64, 4)), (1304, (64, 8)), (1305, (32, 8)), (1306, (64, 4))):
         prob = wl.random_smooth_patch(2, (121, ny), seed=ny)
         prob.bc = ((R, O), (O, R), (0, 0))
@@ -75,8 +76,8 @@ def test_chunk_remainders(prec, solver):
 
 
 def test_switch_across_chunks():
-    """A shock along y met by chunks of three rows (transverse bits of the
-    rows above and below a chunk edge), both precisions."""
+    """A shock along y met by chunks of two and four rows (transverse bits of
+    the rows above and below a chunk edge), both precisions."""
     n = 1303
     prob = wl.planar_shock(n, 121, amp=0.0)
     W = prob.W.transpose(0, 2, 1)[[0, 2, 1, 3]].copy()
@@ -102,5 +103,58 @@ def test_learned_across_chunks():
         ref = oracle.step(d, U0, dt)
         err = np.abs(p.get_state(hydro.CONSERVED) - ref) / scale(ref)
         # a bf16 operand tie moves a slope by up to 0.4 % (the learned-limiter tests' bars)
+        assert np.mean(err) < 2e-5 and err.max() < 2e-3, (bc, err.max())
+        p.close()
+
+
+def config_rows(p):
+    return int(p.kernel_config().split("rows=")[1])
+
+
+@pytest.mark.parametrize("prec,sizes", [
+    (32, {2: 1025, 3: 5123, 4: 10753, 5: 14851, 6: 23554, 7: 33795, 10: 61440}),
+    (64, {2: 1537, 3: 2051, 4: 7169, 5: 14339, 6: 16385, 7: 20994, 10: 30211, 19: 57857}),
+])
+def test_rows_per_chunk(prec, sizes):
+    """Tall patches of one strip whose chunks have 2 to 10 (FP64 19) rows, a
+    last chunk shorter than the others, walls and gravity."""
+    for rows, ny in sizes.items():
+        prob = wl.random_smooth_patch(2, (5, ny), seed=rows)
+        prob.bc = ((R, O), (O, R), (0, 0))
+        prob.accel = (0.03, -0.1, 0.0)
+        p = hydro.Patch(prob, precision=prec, set_initial=False)
+        assert config_rows(p) == rows, (ny, p.kernel_config())
+        p.close()
+        check(prob, oracle.HLLC, prec)
+
+
+@pytest.mark.parametrize("bc", [((P, P), (P, P)), ((O, R), (R, O)), ((R, R), (P, P))])
+@pytest.mark.parametrize("prec", [32, 64])
+def test_patches_lying_along_x(prec, bc):
+    """128 times as wide as high and more: the chunks of a strip follow each
+    other (one column less than that: the strips of a row), with rows left
+    over and wavefronts past the last chunk."""
+    for n in ((256, 2), (255, 2), (1300, 9), (1151, 9), (5200, 40), (7690, 3)):
+        prob = wl.random_smooth_patch(2, n, seed=n[0])
+        prob.bc = bc + ((0, 0),)
+        for solver in (oracle.HLLC, oracle.HLLC_SWITCH):
+            check(prob, solver, prec)
+
+
+def test_learned_along_x():
+    w = (0.2 * np.random.default_rng(9).normal(size=1249)).astype(np.float32)
+    for bc in (P, O, R):
+        prob = wl.random_smooth_patch(2, (5200, 40), seed=60 + bc, bc=bc)
+        d = oracle.Desc.from_problem(prob, solver=oracle.HLLC, limiter=oracle.LIM_LEARNED, mlp=w.astype(np.float64),
+                                     mlp_bf16=True)
+        p = hydro.Patch(prob, precision=32, limiter=hydro.LIM_LEARNED, set_initial=False)
+        p.set_mlp(w)
+        p.set_state(prob.W)
+        U0 = p.get_state(hydro.CONSERVED)
+        dt = oracle.cfl_dt(d, U0, 0.3)
+        p.step(dt, hydro.HLLC)
+        ref = oracle.step(d, U0, dt)
+        err = np.abs(p.get_state(hydro.CONSERVED) - ref) / scale(ref)
+        # (the bars of test_learned_across_chunks)
         assert np.mean(err) < 2e-5 and err.max() < 2e-3, (bc, err.max())
         p.close()
