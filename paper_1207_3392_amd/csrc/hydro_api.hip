@@ -1175,15 +1175,14 @@ hy_status hy_batch_set_state(hy_batch *b, int i, int kind, const double *host)
     return HY_OK;
 }
 
-// The queue: every tube by descending time estimate, the tubes that a team
-// shares first.  A team's members must run together, so all of them stand
-// among the first nblocks entries.  A smaller bound on the longest tube costs
-// more of the machine (a shared step pays for its exchange); of 16 bounds the
-// one whose simulated schedule ends first is taken.  Estimates only: the
-// results do not depend on the split.
-static hy_status batch_order(hy_batch *b)
+// The queue for a grid of nblocks workgroups: every tube by descending time
+// estimate, the tubes that a team shares first.  A team's members must run
+// together, so all of them stand among the first nblocks entries.  A smaller
+// bound on the longest tube costs more of the machine (a shared step pays for
+// its exchange); of 16 bounds the one whose simulated schedule ends first is
+// taken.  Estimates only: the results do not depend on the split.
+static std::vector<hy::BatchItem> batch_plan(const hy_batch *b, int nblocks)
 {
-    if (b->order_set) return HY_OK;
     // us per step, measured: 1.7 (448 cells), 2.4 (896), 4.9 (2048), 8.6 (4096),
     // 13.5 (6144) on one workgroup; shared, 2.1 to 2.7 for 128 to 512 cells a
     // member.  Runs by the surcharge of a shared step (512 tubes of 128 .. 4096
@@ -1191,26 +1190,35 @@ static hy_status batch_order(hy_batch *b)
     // 1.5 us 46.1 / 12.5 ms, unshared 78 / 20 ms.
     auto us = [](double cells, int m) { return std::max(1.75, 0.65 + 2.05e-3 * cells / m) + (m > 1 ? 0.6 : 0.0); };
     const int n = b->count;
-    std::vector<double> steps(n), est(n), best_est(n);
-    std::vector<int> parts(n), best_parts(n, 1), ord(n);
-    double longest = 0.0;
+    std::vector<double> steps(n), alone(n), est(n), best_est(n);
+    std::vector<int> most(n), parts(n, 1), best_parts(n, 1), ord(n);
+    double longest = 0.0, total = 0.0;
+    bool gain = false;  // some tube's steps would be faster shared
     for (int i = 0; i < n; ++i) {
-        steps[i] = b->cost[i] / (double)b->d[i].n[0];
-        longest = std::max(longest, steps[i] * us((double)b->d[i].n[0], 1));
+        const double cells = (double)b->d[i].n[0];
+        steps[i] = b->cost[i] / cells;
+        alone[i] = steps[i] * us(cells, 1);
+        longest = std::max(longest, alone[i]);
+        total += alone[i];
+        most[i] = (int)std::min<int64_t>(hy::TEAM_MAX, b->d[i].n[0] / hy::TEAM_MIN_CELLS);
+        gain |= most[i] > 1 && us(cells, most[i]) < us(cells, 1);
     }
-    const int room = std::min(b->nblocks, hy::TEAM_SLOTS);
+    std::iota(ord.begin(), ord.end(), 0);
+    std::sort(ord.begin(), ord.end(), [&](int x, int y) { return alone[x] != alone[y] ? alone[x] > alone[y] : x < y; });
+    best_est = est = alone;
+    const int room = std::min(nblocks, hy::TEAM_SLOTS);
     double best = std::numeric_limits<double>::infinity();
     std::vector<double> busy;
-    for (int k = 0; k < 16; ++k) {
+    // (the search only where it can help: 2000 tubes of 64 cells spent 0.5 ms
+    // on it in front of a run of 0.1 ms)
+    for (int k = 0; k < 16 && gain; ++k) {
         const double bound = longest * std::pow(0.84, (double)k);  // down to 1/14
         int shared = 0;
         for (int i = 0; i < n; ++i) {
-            const double cells = (double)b->d[i].n[0];
-            const int most = (int)std::min<int64_t>(hy::TEAM_MAX, b->d[i].n[0] / hy::TEAM_MIN_CELLS);
             parts[i] = 1;
-            est[i] = steps[i] * us(cells, 1);
-            for (int m = 2; m <= most && est[i] > bound; ++m) {
-                const double t = steps[i] * us(cells, m);
+            est[i] = alone[i];
+            for (int m = 2; m <= most[i] && est[i] > bound; ++m) {
+                const double t = steps[i] * us((double)b->d[i].n[0], m);
                 if (t < est[i]) {
                     parts[i] = m;
                     est[i] = t;
@@ -1219,8 +1227,6 @@ static hy_status batch_order(hy_batch *b)
             if (parts[i] > 1) shared += parts[i];
         }
         if (shared > room) break;  // (a smaller bound shares more)
-        std::iota(ord.begin(), ord.end(), 0);
-        std::sort(ord.begin(), ord.end(), [&](int x, int y) { return est[x] != est[y] ? est[x] > est[y] : x < y; });
         busy.clear();
         double end = 0.0;
         for (int i : ord)
@@ -1228,7 +1234,7 @@ static hy_status batch_order(hy_batch *b)
                 busy.insert(busy.end(), parts[i], est[i]);
                 end = std::max(end, est[i]);
             }
-        busy.resize(b->nblocks, 0.0);
+        busy.resize(nblocks, 0.0);
         std::make_heap(busy.begin(), busy.end(), std::greater<double>());
         for (int i : ord)
             if (parts[i] == 1) {
@@ -1242,8 +1248,8 @@ static hy_status batch_order(hy_batch *b)
             best_parts = parts;
             best_est = est;
         }
+        if (k == 0 && end <= 1.02 * total / nblocks) break;  // unshared, every workgroup is busy to the end
     }
-    std::iota(ord.begin(), ord.end(), 0);
     std::sort(ord.begin(), ord.end(), [&](int x, int y) {
         const bool tx = best_parts[x] > 1, ty = best_parts[y] > 1;
         if (tx != ty) return tx;
@@ -1259,10 +1265,22 @@ static hy_status batch_order(hy_batch *b)
             slot += m;
         }
     }
+    return items;
+}
+
+static hipError_t batch_upload_plan(hy_batch *b, int nblocks)
+{
+    const std::vector<hy::BatchItem> items = batch_plan(b, nblocks);
     b->nitems = (int)items.size();
     hipError_t e = hipMemcpyAsync(b->items, items.data(), sizeof(hy::BatchItem) * items.size(), hipMemcpyHostToDevice,
                                   b->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
+    return e == hipSuccess ? hipStreamSynchronize(b->stream) : e;
+}
+
+static hy_status batch_order(hy_batch *b)
+{
+    if (b->order_set) return HY_OK;
+    const hipError_t e = batch_upload_plan(b, b->nblocks);
     if (e != hipSuccess) return hip_fail(e, "queue order upload");
     b->order_set = true;
     return HY_OK;

@@ -205,3 +205,32 @@ def test_route_of_a_run_changes_nothing(prec):
         assert a.cfl_dt(0.4) == b.cfl_dt(0.4)
         a.close()
         b.close()
+
+
+def test_a_run_after_a_change_costs_little_more():
+    """Setting one of many short tubes anew makes the next run order its
+    queue again, on the host: a small part of the run, not several times it."""
+    import time
+
+    import torch
+
+    pr = tube(64, wl.BC_OUTFLOW, 3)
+    B = hydro.Batch([pr] * 2000)
+
+    def best(fn):
+        out = []
+        for _ in range(12):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            fn()
+            torch.cuda.synchronize()
+            out.append(time.perf_counter() - t)
+        return min(out)
+
+    def again():
+        B.set_state(0, pr.W)
+        B.run_to(0.02, 0.4)
+
+    plain, changed = best(lambda: B.run_to(0.02, 0.4)), best(again)
+    assert changed < 3.0 * plain, (plain, changed)
+    B.close()
