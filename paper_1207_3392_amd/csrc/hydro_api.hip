@@ -1339,18 +1339,14 @@ hy_status hy_batch_autotune(hy_batch *b, double t_end, double cfl, int solver, i
     if (!(t_end > 0.0) || !std::isfinite(t_end)) return fail(HY_EINVAL, "t_end must be finite and > 0");
     if (!(cfl > 0.0) || !std::isfinite(cfl)) return fail(HY_EINVAL, "cfl must be finite and > 0");
     if (solver != HY_HLL && solver != HY_HLLC && solver != HY_HLLC_SWITCH) return fail(HY_EINVAL, "unknown solver");
-    hy_status st = batch_order(b);
-    if (st != HY_OK) return st;
     hy::BatchCtl c{};
     c.max_steps = kBatchMaxSteps;
-    c.nitems = b->nitems;
     c.t_end = t_end;
     c.cfl = cfl;
     const size_t ubytes = sizeof(float) * 3 * (size_t)b->ntot;
     // the state is kept in the read-back scratch and restored before every
     // trial and at the end
     hipError_t e = hipMemcpyAsync(b->W, b->U, ubytes, hipMemcpyDeviceToDevice, b->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(b->ctl, &c, sizeof(c), hipMemcpyHostToDevice, b->stream);
     double bms = 1e300;
     int bbt = b->bt;
     std::vector<int> bts;
@@ -1358,7 +1354,12 @@ hy_status hy_batch_autotune(hy_batch *b, double t_end, double cfl, int solver, i
     for (int bt : {1024, 512, 256})
         if (bt != b->bt) bts.push_back(bt);
     for (int bt : bts) {
+        // each size with the split that its own number of workgroups would run
         const int nb = batch_grid(b, bt);
+        b->order_set = false;
+        if (e == hipSuccess) e = batch_upload_plan(b, nb);
+        c.nitems = b->nitems;
+        if (e == hipSuccess) e = hipMemcpyAsync(b->ctl, &c, sizeof(c), hipMemcpyHostToDevice, b->stream);
         if (e == hipSuccess) e = hipMemcpyAsync(b->U, b->W, ubytes, hipMemcpyDeviceToDevice, b->stream);
         if (e == hipSuccess) e = hy::launch_batch_reset(b->ctl, b->join, b->mail, b->status, b->count, b->stream);
         if (e == hipSuccess) e = hipEventRecord(b->ev[0], b->stream);
@@ -1382,7 +1383,6 @@ hy_status hy_batch_autotune(hy_batch *b, double t_end, double cfl, int solver, i
     if (bbt != b->bt) {
         b->bt = bbt;
         b->nblocks = batch_grid(b, bbt);
-        b->order_set = false;  // (the split depends on how many workgroups run at once)
         batch_drop_graphs(b);  // recaptured with the new workgroup size at the next run
     }
     if (best_bt) *best_bt = bbt;

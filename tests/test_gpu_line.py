@@ -207,6 +207,35 @@ def test_route_of_a_run_changes_nothing(prec):
         b.close()
 
 
+def test_autotune_times_each_size_as_it_would_run():
+    """Each workgroup size is tried with the split of its own number of
+    workgroups: the size that autotune keeps runs within 20 % of the fastest,
+    whichever size it started from (with the starting size's split for all, it
+    kept 256 threads here, 1.45 times slower)."""
+    a, b = tube(1700, wl.BC_OUTFLOW, 1), tube(100, wl.BC_OUTFLOW, 2)
+    B = hydro.Batch([a] * 200 + [b] * 500)
+
+    def ms(threads):
+        B.set_block(threads)
+        out = []
+        for _ in range(3):
+            for i, pr in enumerate(B.problems):
+                B.set_state(i, pr.W)
+            B.run_to(0.05, 0.4)
+            out.append(B.last_ms())
+        return min(out)
+
+    own = {t: ms(t) for t in (256, 512, 1024)}
+    for start in (256, 1024):
+        B.set_block(start)
+        for i, pr in enumerate(B.problems):
+            B.set_state(i, pr.W)
+        kept, t = B.autotune(0.05, 0.4)
+        assert B.block() == kept
+        assert own[kept] <= 1.2 * min(own.values()) and t <= 1.2 * min(own.values()), (start, kept, t, own)
+    B.close()
+
+
 def test_a_run_after_a_change_costs_little_more():
     """Setting one of many short tubes anew makes the next run order its
     queue again, on the host: a small part of the run, not several times it."""
