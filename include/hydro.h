@@ -254,7 +254,8 @@ hy_status hy_batch_workspace_bytes(const hy_patch_desc *descs, int count, size_t
 hy_status hy_batch_init(const hy_patch_desc *descs, int count, void *dev_workspace, size_t bytes,
                         void *hip_stream, hy_batch **out);
 /* State of tube i (3 x n FP64, SoA); host_soa may be reused on return (the
- * upload is enqueued from pinned staging of the handle). */
+ * upload is enqueued from pinned staging of the handle).  HY_EDEVICE while the
+ * stream is being captured. */
 hy_status hy_batch_set_state(hy_batch *b, int i, int kind, const double *host_soa);
 /* Advance every tube from t = 0 to t_end; asynchronous (one graph launch). */
 hy_status hy_batch_run_to(hy_batch *b, double t_end, double cfl, int solver);

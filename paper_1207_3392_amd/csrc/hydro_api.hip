@@ -1137,8 +1137,13 @@ hy_status hy_batch_set_state(hy_batch *b, int i, int kind, const double *host)
     if (i < 0 || i >= b->count) return fail(HY_EINVAL, "tube index out of range");
     if (kind != HY_PRIMITIVE && kind != HY_CONSERVED) return fail(HY_EINVAL, "unknown state kind");
     const int64_t n = b->d[i].n[0];
-    hipError_t e = hipSuccess;
-    if (b->uploading[i]) {  // (set twice in a row: the first upload must have been read)
+    // (captured, the upload would read at each replay what the staging then
+    // holds, and this call would have set nothing)
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    hipError_t e = hipStreamIsCapturing(b->stream, &cap);
+    if (e == hipSuccess && cap != hipStreamCaptureStatusNone)
+        return fail(HY_EDEVICE, "tube upload: the stream is being captured");
+    if (e == hipSuccess && b->uploading[i]) {  // (set twice in a row: the first upload must have been read)
         e = hipStreamSynchronize(b->stream);
         std::fill(b->uploading.begin(), b->uploading.end(), 0);
     }

@@ -263,3 +263,22 @@ def test_a_run_after_a_change_costs_little_more():
     plain, changed = best(lambda: B.run_to(0.02, 0.4)), best(again)
     assert changed < 3.0 * plain, (plain, changed)
     B.close()
+
+
+def test_setting_a_tube_is_refused_under_capture():
+    import torch
+
+    pr = tube(100, wl.BC_OUTFLOW, 4)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        B = hydro.Batch([pr, pr])
+        before = B.get_state(0)
+        x = torch.zeros(4, device="cuda")
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            x += 1.0
+            with pytest.raises(hydro.HydroError):
+                B.set_state(0, 2.0 * pr.W)
+        g.replay()
+        assert np.array_equal(B.get_state(0), before) and x.sum().item() == 4.0
+        B.close()
