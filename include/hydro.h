@@ -267,9 +267,9 @@ hy_status hy_batch_get_block(hy_batch *b, int *threads);
 /* Autotuner: runs the whole batch from its current state to t_end with each
  * workgroup size (the queue order and every tube's dt loop as in
  * hy_batch_run_to), times each launch with HIP events, keeps the fastest
- * (the current size unless another is at least 2 % faster) and restores
- * the state and the per-tube status as they were before; best
- * and best_ms may be NULL.  Synchronising. */
+ * (the current size unless another is at least 2 % faster), restores
+ * the state as it was before and leaves every tube's status at no step
+ * taken; best and best_ms may be NULL.  Synchronising. */
 hy_status hy_batch_autotune(hy_batch *b, double t_end, double cfl, int solver, int *best_threads, double *best_ms);
 /* Milliseconds of the last hy_batch_run_to launch (HIP events); synchronising. */
 hy_status hy_batch_last_ms(hy_batch *b, double *ms);
@@ -278,6 +278,9 @@ hy_status hy_batch_get_state(hy_batch *b, int i, int kind, double *host_soa_out)
 /* Steps taken and time reached by tube i in the last run (0 steps at t = 0
  * before the first run); synchronising. */
 hy_status hy_batch_status(hy_batch *b, int i, int64_t *steps, double *t);
+/* Workgroups that shared tube i in the last run (1: it ran on one; 0 before the
+ * first run); synchronising. */
+hy_status hy_batch_members(hy_batch *b, int i, int *members);
 hy_status hy_batch_destroy(hy_batch *b);
 
 /* ---------------------------------------------------------------------

@@ -292,6 +292,7 @@ __global__ void __launch_bounds__(64 * NW) k_batch(const TubeDesc *__restrict__ 
             if (rank == 0) {
                 status[it.tube].steps = steps;
                 status[it.tube].t = t;
+                status[it.tube].members = M;
             }
         }
         __syncthreads();

@@ -21,6 +21,8 @@ struct TubeStatus {
     int steps;
     int err;      // bit 0: rho <= 0, p <= 0 or non-finite met; bit 1: stopped early (dt not > 0 or step cap)
     double t;
+    int members;  // workgroups that shared the tube in its last run
+    int pad;
 };
 
 // Teams: a long tube may be split over up to TEAM_MAX workgroups, each of

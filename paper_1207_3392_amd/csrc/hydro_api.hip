@@ -1463,6 +1463,18 @@ hy_status hy_batch_status(hy_batch *b, int i, int64_t *steps, double *t)
     return HY_OK;
 }
 
+hy_status hy_batch_members(hy_batch *b, int i, int *members)
+{
+    if (!b || !members) return fail(HY_EINVAL, "null argument");
+    if (i < 0 || i >= b->count) return fail(HY_EINVAL, "tube index out of range");
+    hy::TubeStatus ts{};
+    hipError_t e = hipMemcpyAsync(&ts, b->status + i, sizeof(ts), hipMemcpyDeviceToHost, b->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
+    if (e != hipSuccess) return hip_fail(e, "status download");
+    *members = ts.members;
+    return HY_OK;
+}
+
 hy_status hy_batch_destroy(hy_batch *b)
 {
     if (!b) return HY_OK;

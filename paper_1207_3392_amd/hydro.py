@@ -134,6 +134,7 @@ EXTRA_SIGNATURES = {
     "hy_batch_autotune": [_P, ctypes.c_double, ctypes.c_double, ctypes.c_int, ctypes.POINTER(ctypes.c_int), _dp],
     "hy_batch_get_state": [_P, ctypes.c_int, ctypes.c_int, _dp],
     "hy_batch_status": [_P, ctypes.c_int, _i64p, _dp],
+    "hy_batch_members": [_P, ctypes.c_int, ctypes.POINTER(ctypes.c_int)],
     "hy_batch_destroy": [_P],
     "hy_lim_sample_count": [_P, _i64p],
     "hy_lim_samples_scratch_bytes": [_P, ctypes.POINTER(ctypes.c_size_t)],
@@ -480,6 +481,12 @@ class Batch:
         t = ctypes.c_double(0.0)
         check(lib().hy_batch_status(self.handle, int(i), ctypes.byref(steps), ctypes.byref(t)), "batch_status")
         return steps.value, t.value
+
+    def members(self, i: int) -> int:
+        """Workgroups that shared tube i in the last run."""
+        v = ctypes.c_int()
+        check(lib().hy_batch_members(self.handle, int(i), ctypes.byref(v)), "batch_members")
+        return v.value
 
     def close(self):
         if getattr(self, "handle", None):

@@ -52,9 +52,9 @@ def test_tubes_at_chunk_edges(solver):
 
 @pytest.mark.parametrize("bc", KINDS + ((1, 2),))
 def test_shared_tubes_equal_unshared(bc):
-    """A tube that a team of workgroups shares equals, bit for bit, the same
-    tube among so many that none is shared, at slices whose last chunk has 1
-    to 4 cells and others."""
+    """A tube alone, which a team of workgroups shares from some 830 cells on,
+    equals, bit for bit, the same tube among so many that none is shared, and
+    (up to 1023 cells) the oracle."""
     for n in (256, 257, 370, 459, 1023, 1795, 6144):
         pr = tube(n, bc, n)
         t_end = 12.0 / n / 3.0
@@ -282,3 +282,76 @@ def test_setting_a_tube_is_refused_under_capture():
         g.replay()
         assert np.array_equal(B.get_state(0), before) and x.sum().item() == 4.0
         B.close()
+
+
+@pytest.mark.parametrize("threads", [256, 512, 1024])
+def test_teams_at_slice_edges(threads):
+    """A tube that a team shares (the members that ran are asked for) equals
+    the same tube on one workgroup, bit for bit, where the members' slices end
+    in a chunk of 1, 2, 3 or 4 cells (copies then reach past the chunk before),
+    of other counts and of all 56, for every kind of end and workgroup size."""
+    ends = set()
+    for k, n in enumerate((897, 898, 900, 903, 904, 1351, 1353, 5555, 5566, 5577, 5588, 5590, 6144)):
+        bc = (KINDS + ((1, 2),))[k % 4]
+        t_end = 12.0 / n / 3.0
+        for b in (bc, wl.BC_PERIODIC):
+            pr = tube(n, b, n)
+            one, many = hydro.Batch([pr]), hydro.Batch([pr] * 600)
+            for B in (one, many):
+                B.set_block(threads)
+                B.run_to(t_end, 0.4, hydro.HLLC)
+            M = one.members(0)
+            assert M > 1 and all(many.members(i) == 1 for i in (0, 300, 599)), (n, M)
+            ends |= {(n // M + (r < n % M)) % 56 for r in range(M)}
+            for i in (0, 599):
+                assert many.status(i) == one.status(0)
+                assert np.array_equal(many.get_state(i, hydro.CONSERVED), one.get_state(0, hydro.CONSERVED)), (n, b, M)
+            one.close()
+            many.close()
+    assert {0, 1, 2, 3, 4} <= ends and len(ends) > 6, ends
+
+
+def test_a_bad_state_in_one_share_of_a_team():
+    """A negative pressure in a cell of one member's share: that tube reports
+    it, the others are as in a batch without it."""
+    good, bad = tube(1795, wl.BC_OUTFLOW, 5), tube(5555, wl.BC_OUTFLOW, 6)
+    bad.W = np.array(bad.W, copy=True)
+    bad.W[2].ravel()[3000] = -0.5
+    t_end = 12.0 / 5555 / 3.0
+    A, B = hydro.Batch([good, good]), hydro.Batch([good, bad, good])
+    for x in (A, B):
+        x.run_to(t_end, 0.4)
+    assert B.members(1) > 1
+    for call in (lambda: B.get_state(1), lambda: B.status(1)):
+        with pytest.raises(hydro.HydroError) as err:
+            call()
+        assert err.value.status == hydro.HY_ESTATE
+    for i, j in ((0, 0), (1, 2)):
+        assert np.array_equal(A.get_state(i, hydro.CONSERVED), B.get_state(j, hydro.CONSERVED))
+        assert A.status(i) == B.status(j)
+    B.set_state(1, tube(5555, wl.BC_OUTFLOW, 6).W)
+    B.run_to(t_end, 0.4)  # the latch is the run's
+    assert B.status(1)[1] == pytest.approx(t_end, rel=1e-12)
+    A.close()
+    B.close()
+
+
+@pytest.mark.parametrize("prec", [32, 64])
+def test_a_bad_state_in_a_run_of_steps(prec):
+    """A state that turns bad between the first and the last step of one
+    launch is reported, by a run of steps as by the stage kernels."""
+    for timing in (False, True):
+        p = hydro.Patch(tube(300, wl.BC_PERIODIC, 7), precision=prec)
+        p.set_timing(timing)
+        p.advance(3, 0.4)
+        p.get_state()
+        p.step(40.0 * p.cfl_dt(0.4))
+        p.advance(5, 0.4)
+        for call in (p.get_state, p.time, lambda: p.cfl_dt(0.4)):
+            with pytest.raises(hydro.HydroError) as err:
+                call()
+            assert err.value.status == hydro.HY_ESTATE
+        p.set_state(p.problem.W)
+        p.advance(5, 0.4)
+        assert np.all(np.isfinite(p.get_state()))
+        p.close()
