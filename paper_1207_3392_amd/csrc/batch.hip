@@ -201,10 +201,10 @@ __global__ void __launch_bounds__(64 * NW) k_batch(const TubeDesc *__restrict__ 
                     }
                 }
             }
-            rate = wave_max(rate);
+            rate = lanes_max(rate);
             if (lane == 0) sRate[tag & 1u][wave] = rate;
             __syncthreads();
-            float r = wave_max(lane < NW ? sRate[tag & 1u][lane] : 0.f);
+            float r = lanes_max(lane < NW ? sRate[tag & 1u][lane] : 0.f);
             if (M > 1 && mailer) {
                 // this workgroup's rate out; the neighbours' cells (lanes 0 ..
                 // 7, three words each) and every member's rate (lanes 8 ..) in
@@ -232,7 +232,7 @@ __global__ void __launch_bounds__(64 * NW) k_batch(const TubeDesc *__restrict__ 
 #pragma unroll
                     for (int v = 0; v < 3; ++v) edge[ln.c_word(ln.nch, lane) + v] = x[v];
                 }
-                r = wave_max(rt ? x[0] : 0.f);
+                r = lanes_max(rt ? x[0] : 0.f);
                 if (lane == 0) sAll = r;
             }
             // stage 1's fluxes need neither dt nor, away from the ends, the mail

@@ -23,29 +23,6 @@ constexpr int LINE_OWN = 56;  // cells a chunk owns
 constexpr int LINE_H = 4;     // copies on either side
 constexpr int LINE_EDGE = 8 * 3;  // LDS words per chunk: its first four cells, its last four
 
-// Maximum over the wavefront (x >= 0), in every lane: within rows of 16, then
-// row 0 into 1 and 2 into 3, then rows 0-1 into 3; lane 63 holds it.
-__device__ __forceinline__ float wave_max(float x)
-{
-#define HY_MAX_STEP(ctrl, rows) \
-    x = fmaxf(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), ctrl, rows, 0xf, false)));
-    HY_MAX_STEP(0x111, 0xf)  // row_shr:1, 2, 4, 8
-    HY_MAX_STEP(0x112, 0xf)
-    HY_MAX_STEP(0x114, 0xf)
-    HY_MAX_STEP(0x118, 0xf)
-    HY_MAX_STEP(0x142, 0xa)  // row_bcast:15
-    HY_MAX_STEP(0x143, 0xc)  // row_bcast:31
-#undef HY_MAX_STEP
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
-}
-__device__ __forceinline__ double wave_max(double x)
-{
-    const unsigned long long m = row_max((unsigned long long)__double_as_longlong(x));
-    const unsigned long long a = lane_u64(m, 0), b = lane_u64(m, 16), c = lane_u64(m, 32), d = lane_u64(m, 48);
-    const unsigned long long e = a > b ? a : b, f = c > d ? c : d;
-    return __longlong_as_double((long long)(e > f ? e : f));
-}
-
 __device__ __forceinline__ float lane_value(float x, int l)
 {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));

@@ -45,11 +45,11 @@ __global__ void __launch_bounds__(64 * NW) k_line(const StageArgs<T> a, int nste
         if constexpr (CPW * NW > 32) ln.fresh();
         ln.send(edge);
         if (s > 0) {
-            rate = wave_max(rate);
+            rate = lanes_max(rate);
             if (lane == 0) sRate[s & 1][wave] = rate;
         }
         __syncthreads();
-        if (s > 0) rmax = (double)wave_max(lane < NW ? sRate[s & 1][lane] : T(0));
+        if (s > 0) rmax = (double)lanes_max(lane < NW ? sRate[s & 1][lane] : T(0));
         double dt = a.dt_host;
         if (a.dt_mode == DT_DEVICE) {
             dt = fmin(a.cfl / rmax, a.t_end - t);
@@ -80,11 +80,11 @@ __global__ void __launch_bounds__(64 * NW) k_line(const StageArgs<T> a, int nste
             for (int v = 0; v < 3; ++v) u[v * a.vstride + ln.cell(k)] = ln.U[k][v];
     }
     if (ln.bad) atomicOr(&a.ctl->err, 1u);
-    rate = wave_max(rate);
+    rate = lanes_max(rate);
     if (lane == 0) sRate[nsteps & 1][wave] = rate;
     __syncthreads();
     if (wave == 0) {
-        const double m = (double)wave_max(lane < NW ? sRate[nsteps & 1][lane] : T(0));
+        const double m = (double)lanes_max(lane < NW ? sRate[nsteps & 1][lane] : T(0));
         const int par = a.parity ^ (nsteps & 1);
         if (lane < RATE_SLOTS)
             a.ctl->rate[par][lane * RATE_STRIDE] = lane == 0 && m > 0.0 ? (unsigned long long)__double_as_longlong(m) : 0ull;
