@@ -82,12 +82,12 @@ __global__ void __launch_bounds__(BX *BY, sizeof(T) == 8 && SOLVER == SOLVER_HLL
     constexpr int IP = ND + 1;
     constexpr int NT = BX * BY;
     static_assert(NT % 64 == 0, "plane tiles are whole wavefronts");
-    constexpr int RY = (ND >= 2) ? BY + 4 : 1;  // LDS rows of primitives (2-cell halo in y)
-    constexpr int OY = (ND >= 2) ? 2 : 0;       // row offset of the tile in LDS
+    constexpr int RY = (ND == 3) ? BY + 4 : 1;  // LDS rows of primitives (2-cell halo in y)
+    constexpr int OY = (ND == 3) ? 2 : 0;       // row offset of the tile in LDS
     constexpr int WX = BX + 4;                  // LDS columns (2-cell halo in x)
-    constexpr int SYR = (ND >= 2) ? BY + 2 : 1;
-    constexpr int FYR = (ND >= 2) ? BY + 1 : 1;
-    constexpr int HROW = (ND >= 2) ? 4 * WX : 0;  // halo rows -2, -1, BY, BY+1 (full width)
+    constexpr int SYR = (ND == 3) ? BY + 2 : 1;
+    constexpr int FYR = (ND == 3) ? BY + 1 : 1;
+    constexpr int HROW = (ND == 3) ? 4 * WX : 0;  // halo rows -2, -1, BY, BY+1 (full width)
     constexpr int NH = HROW + 4 * BY;             // + halo columns -2, -1, BX, BX+1 of each tile row
     constexpr int HPT = (NH + NT - 1) / NT;       // halo cells per thread
 
@@ -98,17 +98,17 @@ __global__ void __launch_bounds__(BX *BY, sizeof(T) == 8 && SOLVER == SOLVER_HLL
     __shared__ T sFy[NP][FYR][BX];      // y faces 0 .. BY
     __shared__ int sMap[WX + RY];       // mapped x of columns -2 .. BX+1, then mapped y of rows -2 .. BY+1
     // HLLC switch: the shock-detector bits of the current plane (cells of
-    // rows -1 .. BY and columns -1 .. BX, corners unused), and in 3D the
-    // pressure and in-plane velocities of the next plane over the same cells
+    // rows -1 .. BY and columns -1 .. BX, corners unused), and the pressure
+    // and in-plane velocities of the next plane over the same cells
     constexpr bool SW = SOLVER == SOLVER_HLLC_SWITCH;
-    constexpr bool SW3 = SW && ND == 3;
+    static_assert(ND == 3 || (ND == 1 && !SW), "3D, and 1D without the switch");
     __shared__ uint8_t sB[SW ? BY + 2 : 1][SW ? BX + 2 : 1];
-    __shared__ T sN[SW3 ? 3 : 1][SW3 ? BY + 2 : 1][SW3 ? BX + 2 : 1];
-    // (3D switch) p and v_z of the plane below the current one, own and ring
+    __shared__ T sN[SW ? 3 : 1][SW ? BY + 2 : 1][SW ? BX + 2 : 1];
+    // (switch) p and v_z of the plane below the current one, own and ring
     // cells: each thread reads and rewrites only its own cells' entries
-    __shared__ T sC[SW3 ? 2 : 1][SW3 ? BY + 2 : 1][SW3 ? BX + 2 : 1];
-    // (3D switch) v_z of the ring cells in the next plane (p sits in sN)
-    __shared__ T sV[SW3 ? BY + 2 : 1][SW3 ? BX + 2 : 1];
+    __shared__ T sC[SW ? 2 : 1][SW ? BY + 2 : 1][SW ? BX + 2 : 1];
+    // (switch) v_z of the ring cells in the next plane (p sits in sN)
+    __shared__ T sV[SW ? BY + 2 : 1][SW ? BX + 2 : 1];
 
     const int tx = threadIdx.x, ty = threadIdx.y;
     const int tid = ty * BX + tx;
@@ -129,7 +129,7 @@ __global__ void __launch_bounds__(BX *BY, sizeof(T) == 8 && SOLVER == SOLVER_HLL
             return;
         }
     }
-    const int vx = PAD ? a.voff[0] : 0, vy = (PAD && ND >= 2) ? a.voff[1] : 0, vz = (PAD && ND == 3) ? a.voff[2] : 0;
+    const int vx = PAD ? a.voff[0] : 0, vy = (PAD && ND == 3) ? a.voff[1] : 0, vz = (PAD && ND == 3) ? a.voff[2] : 0;
     const int sx = PAD ? a.vm[0] : nx;
     const int plane = PAD ? a.vm[0] * a.vm[1] : nx * ny;
     // a coordinate's storage index: boundary-mapped, or (a view) shifted by
@@ -154,7 +154,7 @@ __global__ void __launch_bounds__(BX *BY, sizeof(T) == 8 && SOLVER == SOLVER_HLL
         bzi = rest / a.tiles_y;
     }
     const int x0 = bxi * BX;
-    const int y0 = (ND >= 2) ? byi * BY : 0;
+    const int y0 = (ND == 3) ? byi * BY : 0;
     const int z0 = (ND == 3) ? bzi * a.zchunk : 0;
     const int nplanes = (ND == 3) ? (z0 + a.zchunk <= nz ? a.zchunk : nz - z0) : 1;
     const T gamma = a.gamma, gm1 = a.gm1, igm1 = a.inv_gm1;
@@ -190,7 +190,7 @@ __global__ void __launch_bounds__(BX *BY, sizeof(T) == 8 && SOLVER == SOLVER_HLL
         bool f = false;
         int m = 0;
         if (i < WX) m = smap(x0 + i - 2, nx, vx, a.bc[0][0], a.bc[0][1], f);
-        else if (ND >= 2) m = smap(y0 + (i - WX) - 2, ny, vy, a.bc[1][0], a.bc[1][1], f);
+        else if (ND == 3) m = smap(y0 + (i - WX) - 2, ny, vy, a.bc[1][0], a.bc[1][1], f);
         sMap[i] = m | (f ? FLIP : 0);
     }
 
@@ -214,7 +214,7 @@ __global__ void __launch_bounds__(BX *BY, sizeof(T) == 8 && SOLVER == SOLVER_HLL
 
     // own column: mapped (the unused columns of partial tiles hold ghost values)
     const int xm = sMap[tx + 2];
-    const int ym = (ND >= 2) ? sMap[WX + ty + 2] : 0;
+    const int ym = (ND == 3) ? sMap[WX + ty + 2] : 0;
     const bool fxo = (xm & FLIP) != 0, fyo = (ym & FLIP) != 0;
     const unsigned colo = (unsigned)((ym & IDX) * sx + (xm & IDX));  // (a valid own cell maps to itself)
     const int gx = x0 + tx, gy = y0 + ty;
@@ -241,7 +241,7 @@ __global__ void __launch_bounds__(BX *BY, sizeof(T) == 8 && SOLVER == SOLVER_HLL
                 col = cc < 2 ? cc - 2 : BX + cc - 2;
             }
             const int hx = sMap[col + 2];
-            const int hy = (ND >= 2) ? sMap[WX + row + 2] : 0;
+            const int hy = (ND == 3) ? sMap[WX + row + 2] : 0;
             hoff[j] = (unsigned)((hy & IDX) * sx + (hx & IDX));
             hlds[j] = ((row + OY) * WX + col + 2) | ((hx & FLIP) ? 1 << 28 : 0) | ((hy & FLIP) ? 1 << 29 : 0);
         }
@@ -278,7 +278,7 @@ __global__ void __launch_bounds__(BX *BY, sizeof(T) == 8 && SOLVER == SOLVER_HLL
     // x and y bits of the cell at tile (row r, column c) of the current plane
     auto bits_w = [&](int r, int c) -> unsigned {
         unsigned b = shock(sW[IP][r + OY][c + 1], sW[IP][r + OY][c + 3], sW[1][r + OY][c + 1], sW[1][r + OY][c + 3]);
-        if constexpr (ND >= 2)
+        if constexpr (ND == 3)
             b |= shock(sW[IP][r + OY - 1][c + 2], sW[IP][r + OY + 1][c + 2], sW[2][r + OY - 1][c + 2],
                        sW[2][r + OY + 1][c + 2])
                  << 1;
@@ -286,7 +286,7 @@ __global__ void __launch_bounds__(BX *BY, sizeof(T) == 8 && SOLVER == SOLVER_HLL
     };
     // x and y bits of the own cell in the plane held by sN
     auto bits_n = [&]() -> unsigned {
-        if constexpr (SW3) {
+        if constexpr (SW) {
             return (unsigned)shock(sN[0][ty + 1][tx], sN[0][ty + 1][tx + 2], sN[1][ty + 1][tx], sN[1][ty + 1][tx + 2]) |
                    ((unsigned)shock(sN[0][ty][tx + 1], sN[0][ty + 2][tx + 1], sN[2][ty][tx + 1], sN[2][ty + 2][tx + 1])
                     << 1);
@@ -302,13 +302,15 @@ __global__ void __launch_bounds__(BX *BY, sizeof(T) == 8 && SOLVER == SOLVER_HLL
     bool mir = false;
 #pragma unroll
     for (int q = 0; q < ND; ++q) mir |= (a.bc[q][0] == BC_REFLECT) | (a.bc[q][1] == BC_REFLECT);
-    const bool cubic = (ND < 2 || a.idx[1] == a.idx[0]) && (ND < 3 || a.idx[2] == a.idx[0]);
+    const bool cubic = (ND == 1 || a.idx[1] == a.idx[0]) && (ND == 1 || a.idx[2] == a.idx[0]);
 
     auto to_w = [&](const T (&u)[NP], T (&w)[NP], bool fx, bool fy, bool fz) {
         bad |= !to_prim<ND>(u, w, gm1);
         if (fx) w[1] = -w[1];
-        if constexpr (ND >= 2) { if (fy) w[2] = -w[2]; }
-        if constexpr (ND == 3) { if (fz) w[3] = -w[3]; }
+        if constexpr (ND == 3) {
+            if (fy) w[2] = -w[2];
+            if (fz) w[3] = -w[3];
+        }
     };
     auto zoff = [&](int z, bool &fz) -> unsigned {
         if constexpr (ND == 3) return (unsigned)(smap(z, nz, vz, a.bc[2][0], a.bc[2][1], fz) * plane);
@@ -319,7 +321,7 @@ __global__ void __launch_bounds__(BX *BY, sizeof(T) == 8 && SOLVER == SOLVER_HLL
         for (int v = 0; v < NP; ++v) out[v] = fma_(h, s[v], w[v]);
     };
     // the ring cell of this thread at plane z: pressure and the three
-    // velocities, mirror signs applied (3D switch)
+    // velocities, mirror signs applied (switch)
     auto ring_prim = [&](int z, int r, int c, T &p, T &vxr, T &vyr, T &vzr) {
         bool fz = false;
         T u[NP], w[NP];
@@ -360,7 +362,7 @@ __global__ void __launch_bounds__(BX *BY, sizeof(T) == 8 && SOLVER == SOLVER_HLL
         face_state(wm1, sm1, hs, fl);
         face_state(WA, SA, -hs, fr);
         bool hll = false;
-        if constexpr (SW3) {
+        if constexpr (SW) {
             // the face below the chunk: x and y bits of planes z0 - 1 and z0
             // (their in-plane neighbours through sN, one plane at a time)
             T p, vxr, vyr, vzr;
@@ -444,19 +446,19 @@ __global__ void __launch_bounds__(BX *BY, sizeof(T) == 8 && SOLVER == SOLVER_HLL
 #pragma unroll
                 for (int v = 0; v < NP; ++v) {
                     lsx[v] = (T)at(a.slopes + (int64_t)v * a.vstride, o);
-                    if constexpr (ND >= 2) lsy[v] = (T)at(a.slopes + (int64_t)(NP + v) * a.vstride, o);
+                    if constexpr (ND == 3) lsy[v] = (T)at(a.slopes + (int64_t)(NP + v) * a.vstride, o);
                 }
             } else {  // a ghost column of a partial tile: boundary-mapped slopes
 #pragma unroll
                 for (int v = 0; v < NP; ++v) {
                     lsx[v] = learned_slope<ND>(a, 0, v, gx, gy, kz);
-                    if constexpr (ND >= 2) lsy[v] = learned_slope<ND>(a, 1, v, gx, gy, kz);
+                    if constexpr (ND == 3) lsy[v] = learned_slope<ND>(a, 1, v, gx, gy, kz);
                 }
             }
 #pragma unroll
             for (int v = 0; v < NP; ++v) {
                 sSx[v][ty][tx + 1] = lsx[v];
-                if constexpr (ND >= 2) sSy[v][ty + 1][tx] = lsy[v];
+                if constexpr (ND == 3) sSy[v][ty + 1][tx] = lsy[v];
             }
             // ring slope of cell (rx, ry), boundary mapped (a direct path for
             // the cells inside the domain costs more registers in 3D than the
@@ -465,7 +467,7 @@ __global__ void __launch_bounds__(BX *BY, sizeof(T) == 8 && SOLVER == SOLVER_HLL
 #pragma unroll
                 for (int v = 0; v < NP; ++v) out[v] = learned_slope<ND>(a, q, v, rx, ry, kz);
             };
-            if constexpr (ND >= 2) {
+            if constexpr (ND == 3) {
                 if (tid < 2 * BX) {
                     ring_slope(1, x0 + (tid < BX ? tid : tid - BX), y0 + (tid < BX ? -1 : BY), lry);
 #pragma unroll
@@ -482,10 +484,10 @@ __global__ void __launch_bounds__(BX *BY, sizeof(T) == 8 && SOLVER == SOLVER_HLL
         // ---- phase 0: primitives of plane kz into LDS (own cell + halo) ----
 #pragma unroll
         for (int v = 0; v < NP; ++v) sW[v][ty + OY][tx + 2] = Wk[v];
-        // switch (3D): the next plane's p and in-plane velocities of the own
+        // switch: the next plane's p and in-plane velocities of the own
         // cell and the ring cell (whose p and v_z also give its z bit)
         // (the ring cell's p and v_z there wait in sN's and the z slot of sC)
-        if constexpr (SW3) {
+        if constexpr (SW) {
             sN[0][ty + 1][tx + 1] = Wk1[IP];
             sN[1][ty + 1][tx + 1] = Wk1[1];
             sN[2][ty + 1][tx + 1] = Wk1[2];
@@ -516,7 +518,7 @@ __global__ void __launch_bounds__(BX *BY, sizeof(T) == 8 && SOLVER == SOLVER_HLL
                 T w[NP];
                 to_prim<ND>(hcur[j], w, gm1);
                 if (hlds[j] & (1 << 28)) w[1] = -w[1];
-                if constexpr (ND >= 2) { if (hlds[j] & (1 << 29)) w[2] = -w[2]; }
+                if constexpr (ND == 3) { if (hlds[j] & (1 << 29)) w[2] = -w[2]; }
 #pragma unroll
                 for (int v = 0; v < NP; ++v) sWf[v * RY * WX + (hlds[j] & ((1 << 28) - 1))] = w[v];
             }
@@ -558,7 +560,7 @@ __global__ void __launch_bounds__(BX *BY, sizeof(T) == 8 && SOLVER == SOLVER_HLL
         if (ring1) __builtin_amdgcn_s_setprio(2);
         if constexpr (LIM != LIM_LEARNED) {
             slope_x(ty, tx);
-            if constexpr (ND >= 2) slope_y(ty, tx);
+            if constexpr (ND == 3) slope_y(ty, tx);
         }
         if constexpr (ND == 3) {
             to_w(U2, W2, fxo, fyo, fz2);
@@ -576,7 +578,7 @@ __global__ void __launch_bounds__(BX *BY, sizeof(T) == 8 && SOLVER == SOLVER_HLL
             }
         }
         if constexpr (LIM != LIM_LEARNED) {
-            if constexpr (ND >= 2) {
+            if constexpr (ND == 3) {
                 if (tid < 2 * BX) slope_y(tid < BX ? -1 : BY, tid < BX ? tid : tid - BX);
             }
             if (ering >= 0) slope_x(ering >> 1, (ering & 1) ? BX : -1);
@@ -588,25 +590,21 @@ __global__ void __launch_bounds__(BX *BY, sizeof(T) == 8 && SOLVER == SOLVER_HLL
             // the one below); the own cell's byte also keeps its x and y bits
             // of the next plane in bits 4 and 5 for its z face
             unsigned ob = bits_w(ty, tx);
-            if constexpr (SW3) {
-                ob |= (unsigned)shock(sC[0][ty + 1][tx + 1], Wk1[IP], sC[1][ty + 1][tx + 1], Wk1[3]) << 2;
-                sC[0][ty + 1][tx + 1] = Wk[IP];
-                sC[1][ty + 1][tx + 1] = Wk[3];
-                ob |= bits_n() << 4;
-            }
+            ob |= (unsigned)shock(sC[0][ty + 1][tx + 1], Wk1[IP], sC[1][ty + 1][tx + 1], Wk1[3]) << 2;
+            sC[0][ty + 1][tx + 1] = Wk[IP];
+            sC[1][ty + 1][tx + 1] = Wk[3];
+            ob |= bits_n() << 4;
             sB[ty + 1][tx + 1] = (uint8_t)ob;
             zb = ob;
             if (ringt) {
                 int rr, rc;
                 ring_rc(rr, rc);
                 unsigned rb = bits_w(rr, rc);
-                if constexpr (SW3) {
-                    rb |= (unsigned)shock(sC[0][rr + 1][rc + 1], sN[0][rr + 1][rc + 1], sC[1][rr + 1][rc + 1],
-                                          sV[rr + 1][rc + 1])
-                          << 2;
-                    sC[0][rr + 1][rc + 1] = sW[IP][rr + OY][rc + 2];
-                    sC[1][rr + 1][rc + 1] = sW[3][rr + OY][rc + 2];
-                }
+                rb |= (unsigned)shock(sC[0][rr + 1][rc + 1], sN[0][rr + 1][rc + 1], sC[1][rr + 1][rc + 1],
+                                      sV[rr + 1][rc + 1])
+                      << 2;
+                sC[0][rr + 1][rc + 1] = sW[IP][rr + OY][rc + 2];
+                sC[1][rr + 1][rc + 1] = sW[3][rr + OY][rc + 2];
                 sB[rr + 1][rc + 1] = (uint8_t)rb;
             }
         }
@@ -642,7 +640,7 @@ __global__ void __launch_bounds__(BX *BY, sizeof(T) == 8 && SOLVER == SOLVER_HLL
                 for (int v = 0; v < NP; ++v) asm volatile("" : "+v"(fl[v]), "+v"(fr[v]));
             }
             riemann<ND, 2, decltype(kind)::value>(fl, fr, Fhi, sg, igm1);
-            if constexpr (SW3) return ((zb | (zb >> 4)) & 3u) != 0u;
+            if constexpr (SW) return ((zb | (zb >> 4)) & 3u) != 0u;
             return false;
         };
         if constexpr (ND == 3) redo(face_z(Main{}), [&] { (void)face_z(Hll{}); });
@@ -695,9 +693,9 @@ __global__ void __launch_bounds__(BX *BY, sizeof(T) == 8 && SOLVER == SOLVER_HLL
         // interleaved, which would only raise register pressure
         redo(face_x(ty, tx, Main{}), [&] { (void)face_x(ty, tx, Hll{}); });
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (ND >= 2) redo(face_y(ty, tx, Main{}), [&] { (void)face_y(ty, tx, Hll{}); });
+        if constexpr (ND == 3) redo(face_y(ty, tx, Main{}), [&] { (void)face_y(ty, tx, Hll{}); });
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (ND >= 2) {
+        if constexpr (ND == 3) {
             if (tid < BX) redo(face_y(BY, tid, Main{}), [&] { (void)face_y(BY, tid, Hll{}); });
         }
         if (fe >= 0) redo(face_x(fe, BX, Main{}), [&] { (void)face_x(fe, BX, Hll{}); });
@@ -721,11 +719,9 @@ __global__ void __launch_bounds__(BX *BY, sizeof(T) == 8 && SOLVER == SOLVER_HLL
         }
 #pragma unroll
         for (int v = 0; v < NP; ++v) out[v] = fma_(cdt[0], sFx[v][ty][tx] - sFx[v][ty][tx + 1], out[v]);
-        if constexpr (ND >= 2) {
+        if constexpr (ND == 3) {
 #pragma unroll
             for (int v = 0; v < NP; ++v) out[v] = fma_(cdt[1], sFy[v][ty][tx] - sFy[v][ty + 1][tx], out[v]);
-        }
-        if constexpr (ND == 3) {
 #pragma unroll
             for (int v = 0; v < NP; ++v) out[v] = fma_(cdt[2], Flo[v] - Fhi[v], out[v]);
         }
@@ -796,7 +792,7 @@ template <int ND, typename T, int SOLVER, int STAGE, int LIM, int BX, int BY>
 hipError_t launch_one(const LaunchCfg &cfg, StageArgs<T> a, hipStream_t s)
 {
     a.tiles_x = (int)((a.n[0] + BX - 1) / BX);
-    a.tiles_y = ND >= 2 ? (int)((a.n[1] + BY - 1) / BY) : 1;
+    a.tiles_y = ND == 3 ? (int)((a.n[1] + BY - 1) / BY) : 1;
     const int chunks = ND == 3 ? (int)((a.n[2] + cfg.zchunk - 1) / cfg.zchunk) : 1;
     a.ntiles = a.tiles_x * a.tiles_y * chunks;
     int64_t blocks = a.ntiles;
@@ -846,7 +842,7 @@ hipError_t launch_nd(int solver, int stage, int limiter, const LaunchCfg &cfg, c
     if (solver == SOLVER_HLL) {
         return stage == 1 ? launch_lim<ND, T, 0, 1>(limiter, cfg, a, s) : launch_lim<ND, T, 0, 2>(limiter, cfg, a, s);
     }
-    if constexpr (ND >= 2) {  // in 1D no face is transverse to anything: the switch is HLLC
+    if constexpr (ND == 3) {  // in 1D no face is transverse to anything: the switch is HLLC
         if (solver == SOLVER_HLLC_SWITCH)
             return stage == 1 ? launch_lim<ND, T, 2, 1>(limiter, cfg, a, s) : launch_lim<ND, T, 2, 2>(limiter, cfg, a, s);
     }
