@@ -240,13 +240,13 @@ hipError_t one_step(hy_patch *p, int solver, int dt_mode, double dt, double cfl,
 
 // Whether one launch of m steps on one workgroup (k_line) is the faster way for
 // a 1D patch than two stage launches a step.  Fits to measured times, us, n =
-// 600 .. 5376, HLL and HLLC: k_line takes 2.3 + 5e-4 n a launch and 0.65 + 1.85e-3 n
-// a step (FP64 2.3 + 6e-4 n, 0.9 + 3.7e-3 n), the stages 7.6 a step in a replayed graph
-// and 7.2 to 8.2 launched (FP64 8.6, 8.6 to 9.8).  So long runs take k_line up to
-// 3584 cells (3584: 7.0 to 7.15 against 7.5 in a graph, 8.2 launched; 4480: 8.9
-// against 7.5; FP64 1792: 6.9 to 7.3 against 8.6; 2200 HLLC: 8.9 against 8.7), single steps
-// up to some 1900 (FP64 1250; 1792: 6.7 against 7.3; 2200: 8.0 against 7.3; FP64 1344 8.4
-// against 8.7, 1792 10.1 against 8.8).
+// 600 .. 3584, HLL and HLLC: k_line takes 2.3 + 4.5e-4 n a launch and 0.55 + 1.82e-3 n
+// a step (FP64 2.3 + 5e-4 n, 0.9 + 3.55e-3 n), the stages 7.6 a step in a replayed
+// graph, 7.2 in single steps and 8.0 to 8.6 launched in a row (FP64 8.6, 8.7 and 9.6 to
+// 10).  So long runs take k_line up to 3584 cells (7.0 there against 7.6 in a graph,
+// 8.0 launched; 4480: 8.9 against 7.5; FP64 2200: 8.4 to 9.0 against 8.5 to 8.8 and 9.8,
+// 2700: 10.7 against 8.6), single steps up to some 2100 (1792: 6.6 against 7.2; 2700: 9.1;
+// FP64 1400: 1344 8.3 to 8.6 against 8.7, 1792 10.0 against 8.7).
 // With timing on the stages are launched one by one, so that they can be timed;
 // the two round alike, bit for bit.
 bool takes_line(const hy_patch *p, int m)
@@ -254,8 +254,8 @@ bool takes_line(const hy_patch *p, int m)
     if (p->d.ndim != 1 || p->padded || p->d.limiter != HY_LIM_THETA || (p->timing && !p->capturing)) return false;
     if (p->d.n[0] > hy::LINE_CELLS) return false;
     const double n = (double)p->d.n[0];
-    if (p->d.precision == 64) return 2.3 + 6e-4 * n + m * (0.9 + 3.7e-3 * n) <= m * 8.6;
-    return 2.3 + 5e-4 * n + m * (0.65 + 1.85e-3 * n) <= m * 7.6;
+    if (p->d.precision == 64) return 2.3 + 5e-4 * n + m * (0.9 + 3.55e-3 * n) <= m * 8.9;
+    return 2.3 + 4.5e-4 * n + m * (0.55 + 1.82e-3 * n) <= m * 7.6;
 }
 
 constexpr int kLineSteps = 4096;  // steps per launch at most: a launch stays within some 40 ms
@@ -966,7 +966,7 @@ struct hy_batch {
     unsigned long long *mail = nullptr;
     hy::TubeStatus *status = nullptr;
     float *U = nullptr;
-    float *W = nullptr;  // scratch for primitive read-back
+    float *W = nullptr;  // the state during autotune
     hipStream_t stream = nullptr;
     hipStream_t capture = nullptr;
     hipGraphExec_t exec[2] = {nullptr, nullptr};  // per solver (HLL, HLLC)
@@ -1349,8 +1349,7 @@ hy_status hy_batch_autotune(hy_batch *b, double t_end, double cfl, int solver, i
     c.t_end = t_end;
     c.cfl = cfl;
     const size_t ubytes = sizeof(float) * 3 * (size_t)b->ntot;
-    // the state is kept in the read-back scratch and restored before every
-    // trial and at the end
+    // the state is kept in W and restored before every trial and at the end
     hipError_t e = hipMemcpyAsync(b->W, b->U, ubytes, hipMemcpyDeviceToDevice, b->stream);
     double bms = 1e300;
     int bbt = b->bt;

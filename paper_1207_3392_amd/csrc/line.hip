@@ -2,15 +2,15 @@
 // loop (dt from the device, both Runge-Kutta stages, the CFL rate of the new
 // state) on one workgroup, the state in registers (hy_line.h).
 //
-// What bounds it: the latency of one step's dependent instructions (1.0 us a
-// step of 16 cells, 1.7 of 600), then the vector issue of one compute unit (1.85 us
-// per 1000 cells, FP64 3.7), and per launch the loads, the stores and the ends
+// What bounds it: the latency of one step's dependent instructions (0.9 us a
+// step of 16 cells, 1.6 of 600), then the vector issue of one compute unit (1.8 us
+// per 1000 cells, FP64 3.6), and per launch the loads, the stores and the ends
 // (2.3 us and 0.5 us per 1000 cells).  us per step, HLLC, in runs of 400:
-//   cells               600  1000  1792  2700  3584  4480  5376
-//   FP32 here          1.71  2.55  3.71  5.80  7.15   9.0  10.6
-//   FP32 stage graph   7.72  7.71  7.69  7.77  7.59   7.6   7.6
-//   FP64 here          3.16  4.81  7.27  11.3  13.9
-//   FP64 stage graph   8.78  8.80  8.70  8.80  8.62
+//   cells                    600  1000  1792  2200  2700  3584
+//   FP32 here               1.61  2.39  3.54  4.49  5.62  7.04
+//   FP32 stages, graph      7.72  7.71  7.69  7.80  7.77  7.59
+//   FP64 here               3.16  4.82  7.28  8.96  11.3  13.9
+//   FP64 stages, graph      8.78  8.80  8.70  8.69  8.80  8.62
 // The host (takes_line) sends each run of steps to the faster of the two.
 #include "hy_line.h"
 

@@ -1,8 +1,10 @@
 // strip.hip -- one Runge-Kutta stage of the finite-volume update in 2D.
 //
-// The arithmetic is that of the 3D stage kernel (stage.hip), cell for cell;
-// what differs is who computes what.  A wavefront owns a strip of 60 columns
-// (its 64 lanes are the columns from 2 left of the strip to 2 right of it)
+// The slopes, face states and fluxes are those of the 3D stage kernel
+// (stage.hip; hy_face.h holds both); a cell's change is summed before its state
+// is added, which rounds the state once a stage; and who computes what differs.
+// A wavefront owns a strip of 60 columns (its 64 lanes are the columns from 2
+// left of the strip to 2 right of it)
 // and marches along y over a chunk of rows.  The y stencil lives in
 // registers (two rows of primitives, the left state of the next y face, the
 // carried y flux), so every y face is solved once; the x neighbours are the
@@ -16,8 +18,9 @@
 // ring items, slopes and fluxes through LDS.  Here the redundant work is 4
 // lanes of 64 and, per chunk, the 3 rows and the one face below its first
 // row: 192 instructions per row of a wavefront (205 per cell) in the first
-// stage, where the tile took 475.  Kelvin-Helmholtz 2048^2, FP32, HLLC: 72 us
-// per step against 130; 1024^2 FP64: 61 us.
+// stage, where the tile took 475.  HLLC, us per step in replayed
+// graphs: Kelvin-Helmholtz 2048^2 FP32 83 against 128 with the tiles, a random field
+// of 2048^2 75.5 / 123, of 1024^2 30 / 38, FP64 54 / 111.
 #include "hy_internal.h"
 #include "hy_face.h"
 #include "hy_ride.h"

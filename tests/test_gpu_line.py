@@ -191,8 +191,8 @@ def test_route_of_a_run_changes_nothing(prec):
     t = f"f{prec}"
     line, stage = f"k_line<nd=1,{t}> threads=1024", f"k_stage<nd=1,{t},tile=64x1> zchunk=1"
     names = {32: {1792: line, 2500: line, 3584: line, 3585: stage, 5376: stage},
-             64: {896: line, 1792: line, 2200: stage, 3584: stage}}[prec]
-    for n in (896, 897, 1254, 1256, 1792, 1793, 1960, 2070, 2085, 2200, 2500, 3583, 3584, 3585, 5376):
+             64: {896: line, 1792: line, 2300: stage, 3584: stage}}[prec]
+    for n in (896, 897, 1406, 1408, 1792, 1793, 1960, 2070, 2200, 2252, 2254, 2300, 2500, 3583, 3584, 3585, 5376):
         pr = tube(n, wl.BC_REFLECT, n)
         a, b = hydro.Patch(pr, precision=prec), hydro.Patch(pr, precision=prec)
         b.set_timing(True)
