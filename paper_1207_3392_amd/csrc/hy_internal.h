@@ -17,12 +17,13 @@ constexpr int RATE_STRIDE = 16;  // words between slots
 // atomics on one 128-byte line queue at the memory side (measured: about 7 ns
 // each while the slots shared two lines, 130 us for the 17,920 wavefronts of a
 // 2048^2 launch), so each slot has a line of its own and a workgroup sends one.
+// The rates come last, so that a read-back of the rest need not fetch them.
 struct DevCtl {
     double time[2];
-    unsigned long long rate[2][RATE_SLOTS * RATE_STRIDE];
     unsigned int err;
     unsigned int pad[3];
     double totals[8];
+    unsigned long long rate[2][RATE_SLOTS * RATE_STRIDE];
 };
 
 // LIM_THETA_PADDED: the generalised-minmod limiter on a view of a larger

@@ -8,6 +8,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstddef>
 #include <functional>
 #include <cstdio>
 #include <cstdlib>
@@ -295,9 +296,12 @@ hy_status spectrum_check(hy_patch *p, int *n_out)
     return HY_OK;
 }
 
-hy_status read_ctl(hy_patch *p, hy::DevCtl *out)
+// The control block up to the CFL rates, or with those up to the current
+// parity's slots (8 KB of rates behind every read-back took 0.3 us).
+hy_status read_ctl(hy_patch *p, hy::DevCtl *out, bool rates = false)
 {
-    hipError_t e = hipMemcpyAsync(out, p->ctl, sizeof(hy::DevCtl), hipMemcpyDeviceToHost, p->stream);
+    const size_t bytes = offsetof(hy::DevCtl, rate) + (rates ? (p->parity + 1) * sizeof(out->rate[0]) : 0);
+    hipError_t e = hipMemcpyAsync(out, p->ctl, bytes, hipMemcpyDeviceToHost, p->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
     if (e != hipSuccess) return hip_fail(e, "reading the control block");
     return HY_OK;
@@ -634,7 +638,7 @@ hy_status hy_cfl_dt(hy_patch *p, double cfl, double *dt_out)
     if (!p || !dt_out) return fail(HY_EINVAL, "null argument");
     if (!(cfl > 0.0) || !std::isfinite(cfl)) return fail(HY_EINVAL, "cfl must be finite and > 0");
     hy::DevCtl c;
-    hy_status st = read_ctl(p, &c);
+    hy_status st = read_ctl(p, &c, true);
     if (st != HY_OK) return st;
     unsigned long long rb = 0ull;
     for (int k = 0; k < hy::RATE_SLOTS; ++k) rb = std::max(rb, c.rate[p->parity][k * hy::RATE_STRIDE]);
