@@ -14,8 +14,9 @@
  *  - Device memory is owned by the caller: the library carves everything it
  *    needs out of one workspace the caller allocates (any device allocator,
  *    e.g. a torch uint8 tensor) after asking for its size.  The library itself
- *    allocates only its host-side handle.  hy_destroy frees the handle, never
- *    the workspace.
+ *    allocates only its host-side handle and, for a batch, pinned host staging
+ *    of 12 bytes per cell (held from hy_batch_init to hy_batch_destroy).
+ *    hy_destroy frees the handle, never the workspace.
  *  - Work is enqueued on the caller's HIP stream (passed as void*, NULL =
  *    the default stream) without host synchronisation, except in the calls
  *    marked "synchronising".
@@ -207,7 +208,8 @@ hy_status hy_kernel_config(hy_patch *p, char *buf, size_t len);
  * with the same arithmetic.  Supported tiles: 64x8, 64x4, 32x8 and (FP32)
  * 32x16 in 2D and 3D, 64x1 in 1D; a patch starts with a shape picked from its
  * size (3D: FP32 64x8, FP64 32x8, with the chunks that fill whole rounds of the
- * card, at most 64 planes; 2D: 64x4).  The HLLC -> HLL switch keeps a shape of
+ * card, at most 64 planes; 2D: 64x4; the rows of a 2D wavefront follow from the
+ * size alone).  The HLLC -> HLL switch keeps a shape of
  * its own (3D FP32: 32x8; else the same): hy_get_launch_cfg reports the
  * HLL/HLLC shape, hy_set_launch_cfg sets the shape of every solver,
  * hy_autotune the shape of the solver it tunes. */
@@ -227,9 +229,9 @@ hy_status hy_set_launch_cfg(hy_patch *p, const hy_launch_cfg *cfg);
  * (mean milliseconds per trial) may be NULL.  U^n, the time and the CFL
  * rate of U^n are unchanged; the scratch stage state is overwritten.  A
  * learned-limiter patch needs its weights (its slopes kernel has a fixed
- * shape and is not part of the trial).  Different z chunks may round
- * differently in the last place (the z faces at chunk starts are formed by
- * the chunk's entry code); tiles never change a result.  Synchronising. */
+ * shape and is not part of the trial).  Neither tiles nor chunks change a
+ * result.  In 1D there is one shape, 64x1: best_ms is the stage kernels', also
+ * where runs of steps take one launch.  Synchronising. */
 hy_status hy_autotune(hy_patch *p, int solver, int reps, hy_launch_cfg *best, double *best_ms);
 
 hy_status hy_destroy(hy_patch *p);
@@ -403,8 +405,8 @@ hy_status hy_fmr_set_graph(hy_fmr *f, int on);
 hy_status hy_fmr_conserved_totals(hy_fmr *f, double out[5]);
 /* hy_autotune on every level (over the cells its stages update: a refined
  * level's interior, in the stage kernel's padded mode; its current state);
- * best, when not NULL, receives nlev shapes.  Results do not change beyond
- * the last-place rounding z chunks can bring.  Drops the captured graph.
+ * best, when not NULL, receives nlev shapes.  Results do not change.  Drops
+ * the captured graph.
  * Synchronising. */
 hy_status hy_fmr_autotune(hy_fmr *f, int solver, int reps, hy_launch_cfg *best);
 hy_status hy_fmr_destroy(hy_fmr *f);
