@@ -40,16 +40,16 @@ template <> __device__ __forceinline__ double rcp_<double>(double x)
 // sqrt(p / r), evaluated as p rsqrt(p r).  FP64: y = 1 / sqrt(p r) from the
 // hardware's reciprocal roots of p and of r, not of p r, which leaves the range
 // long before the ratio does (densities and pressures near 1e-155 or 1e155); one
-// Newton step on s = p y, with 1 - p r y^2 formed from p y and r y, leaves about
+// Newton step on s = p y, with p r y^2 formed from p y and r y / 2, leaves about
 // 2^-42, and the residual p - s^2 r, with s r carried in two parts, corrects s to
-// the last rounding: 14 instructions where a division and a root take 25.  (One
+// the last rounding: 13 instructions where a division and a root take 25.  (One
 // reciprocal root of p r saves 1 to 3 % of an FP64 step, 150 x 140 x 130, 10 steps:
-// 2168 us against 2202, and gives a NaN where p r overflows or vanishes.)
+// 2160 us against 2189, and gives a NaN where p r overflows or vanishes.)
 __device__ __forceinline__ float root_ratio(float p, float r) { return p * __builtin_amdgcn_rsqf(p * r); }
 __device__ __forceinline__ double root_ratio(double p, double r)
 {
     const double y = __builtin_amdgcn_rsq(p) * __builtin_amdgcn_rsq(r), h = 0.5 * y, u = p * y;
-    const double s = fma_(fma_(-u, r * y, 1.0), 0.5 * u, u), t = s * r;
+    const double s = u * fma_(-u, r * h, 1.5), t = s * r;
     const double e = fma_(-fma_(s, r, -t), s, fma_(-t, s, p));
     return fma_(e, h, s);
 }

@@ -1192,7 +1192,7 @@ hy_status hy_batch_set_state(hy_batch *b, int i, int kind, const double *host)
 // taken.  Estimates only: the results do not depend on the split.
 static std::vector<hy::BatchItem> batch_plan(const hy_batch *b, int nblocks)
 {
-    // us per step, measured: 1.7 (448 cells), 2.4 (896), 4.9 (2048), 8.6 (4096),
+    // us per step of 1024 threads: 1.7 (448 cells), 2.4 (896), 4.9 (2048), 8.6 (4096),
     // 13.5 (6144) on one workgroup; shared, 2.1 to 2.7 for 128 to 512 cells a
     // member.  Runs by the surcharge of a shared step (512 tubes of 128 .. 4096
     // cells, 310 of 146 .. 2445): 0.6 us 39.1 / 11.7 ms, 1.0 us 38.5 / 12.5 ms,

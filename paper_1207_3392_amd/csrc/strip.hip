@@ -327,23 +327,26 @@ __global__ void __launch_bounds__(512, sizeof(T) == 8 ? 2 : 4) k_strip(const Sta
 
 // Rows per chunk: a short chunk repeats its 3 rows and one face more often, a
 // long one leaves few wavefronts to hide latency with, and a last round over the
-// card's 1024 SIMDs that is nearly empty costs as much as a full one.  The rows
-// are those with the least (1.5 + k) (rows + 1.6), FP64 (0.7 + k) (rows + 2), k the
-// wavefronts on the busiest SIMD: over 54 shapes of 10^4 to 10^7 cells the step is
-// then within 2 % (FP64 7 %) of the best of 1 .. 32 rows, on average 0.2 % (0.8 %).
-// (Rows as the square root of the strips' length, picked before: 15 % and 31 %, on
-// average 2 and 11 %.  us per step, HLLC: FP32 700^2 20.6 -> 17.9, FP64 38.7 -> 30.3;
-// FP64 61 x 4000 32.4 -> 26.1; FP32 2048^2 75.8 and 512^2 14.2 as before.)
+// card's 1024 SIMDs that is nearly empty costs most of a full one.  The rows are
+// those with the least (1 + k) (rows + 1.2), FP64 (0.7 + k) (rows + 2), k the
+// wavefronts on a SIMD, three quarters the busiest one's and one the mean: over 54
+// shapes of 10^4 to 10^7 cells the step is then within 2 % (FP64 7 %) of the best of
+// 1 .. 32 rows, on average 0.1 % (0.8 %).  (Rows as the square root of the strips'
+// length, picked before: 15 % and 31 %, on average 2 and 11 %.  us per step, HLLC: FP32
+// 700^2 20.6 -> 17.9, FP64 38.7 -> 30.3; FP64 61 x 4000 32.4 -> 26.1; FP32 2048^2 75.8 and
+// 512^2 14.2 as before.)
 template <typename T>
 int strip_rows(const int64_t n[3])
 {
     const int ny = (int)n[1], strips = (int)((n[0] + SC - 1) / SC);
-    const float a = sizeof(T) == 4 ? 1.5f : 0.7f, b = sizeof(T) == 4 ? 1.6f : 2.f;
+    const float a = sizeof(T) == 4 ? 1.f : 0.7f, b = sizeof(T) == 4 ? 1.2f : 2.f;
     int best = 1;
     float cost = std::numeric_limits<float>::max();
     for (int r = 1; r <= 32 && r <= ny; ++r) {
-        const int k = (strips * ((ny + r - 1) / r) + 1023) >> 10;
-        const float c = (a + (float)k) * ((float)r + b);
+        const int waves = strips * ((ny + r - 1) / r);
+        const float mean = (float)waves * (1.f / 1024.f);
+        const float k = 0.75f * (float)((waves + 1023) >> 10) + 0.25f * (mean > 1.f ? mean : 1.f);
+        const float c = (a + k) * ((float)r + b);
         if (c < cost) {
             cost = c;
             best = r;

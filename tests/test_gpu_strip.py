@@ -112,8 +112,8 @@ def config_rows(p):
 
 
 @pytest.mark.parametrize("prec,sizes", [
-    (32, {2: 1025, 3: 5123, 4: 10753, 5: 14851, 6: 23554, 7: 33795, 10: 61440}),
-    (64, {2: 1537, 3: 2051, 4: 7169, 5: 14339, 6: 16385, 7: 20994, 10: 30211, 19: 57857}),
+    (32, {2: 1717, 3: 2368, 4: 6185, 5: 9257, 6: 16425, 7: 20521, 10: 50217}),
+    (64, {2: 1065, 3: 2089, 4: 3113, 5: 4137, 6: 10281, 7: 6185, 10: 18473, 19: 57385}),
 ])
 def test_rows_per_chunk(prec, sizes):
     """Tall patches of one strip whose chunks have 2 to 10 (FP64 19) rows, a
